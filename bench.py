@@ -165,7 +165,8 @@ def query_breakdown(q, ab, err, budget, sweep=(10 ** 2, 10 ** 3, 10 ** 4, 10 ** 
 # launch) are compiled from, and those of the m-line kernel: committed HBM
 # counters stay valid while these are unchanged.
 DECODE_SOURCES = ("decode.hip", "decode_impl.h", "decode_nk1.hip", "decode_nk2.hip", "decode_nk4.hip", "decode_nk8.hip",
-                  "decode_nk16.hip", "orbg_device.h", "orbg_internal.h", "orbg_kernels.h", "schedule.hip")
+                  "decode_nk16.hip", "match_impl.h", "first_impl.h", "match_nk1.hip", "match_nk2.hip", "match_nk4.hip",
+                  "match_nk8.hip", "match_nk16.hip", "orbg_device.h", "orbg_internal.h", "orbg_kernels.h", "schedule.hip")
 MLINE_SOURCES = ("mline.hip", "mline_impl.h", "mline_m1.hip", "mline_m2.hip", "mline_m3.hip", "mline_m4.hip", "orbg_mline.h",
                  "orbg_device.h", "orbg_internal.h")
 

@@ -236,6 +236,18 @@ int get_workspace(hipStream_t st, int64_t heavy_need, Workspace** out, int* cus)
     return ORBG_OK;
 }
 
+// Counters and, where the heavy pass may run, its list of blocks.
+int get_decode_space(hipStream_t st, orbg::DecodeArgs* a)
+{
+    Workspace* w = nullptr;
+    const int64_t need = a->p.split_steps > 0 && !orbg::uses_match(*a) ? a->nblocks : 0;
+    const int rc = get_workspace(st, need, &w, &a->cus);
+    if (rc) return rc;
+    a->ctrs = w->ctrs;
+    a->heavy = need > 0 ? w->heavy : nullptr;
+    return ORBG_OK;
+}
+
 orbg::LaunchParams resolve_params(const orbg_launch_params* p, bool ordered)
 {
     orbg::LaunchParams r;
@@ -282,10 +294,10 @@ int keys_per_lane(int n)
     return nk;
 }
 
-// Fills one code descriptor (schedule for `need` queries; build = false: the
-// schedule must exist already).
-int describe(const CodeEntry* c, uint64_t need, hipStream_t st, uint32_t col_base, orbg::CodeDesc* d,
-             bool build = true)
+// Fills one code descriptor of a zeroed table (schedule for `need` >= budget
+// queries; build = false: the schedule must exist already).
+int describe(const CodeEntry* c, uint64_t need, uint64_t budget, hipStream_t st, uint32_t col_base,
+             orbg::CodeDesc* d, bool build = true)
 {
     if (c->n < 63 && need > (1ull << c->n)) need = 1ull << c->n;
     const orbg::Schedule* s = nullptr;
@@ -302,6 +314,21 @@ int describe(const CodeEntry* c, uint64_t need, hipStream_t st, uint32_t col_bas
     d->rows = c->d_rows;
     d->row_base = 0;
     d->sched = s->entries;
+    // match search: codes with at least ORBG_MATCH_M check bits (fewer, and a
+    // search ends within a few steps: 2^m patterns hold a member on average)
+    if (s->match.sets != nullptr && d->m >= ORBG_MATCH_M) {
+        d->sets = s->match.sets;
+        d->below = s->match.below;
+        d->above = s->match.above;
+        const uint64_t lim = budget < s->len ? budget : s->len;
+        auto weight_of = [&](uint64_t query) {
+            int w = 0;
+            while (w < s->wlast && s->match.total[w] < query) ++w;
+            return w;
+        };
+        d->wprefix = weight_of(4096);
+        d->wlim = weight_of(lim);
+    }
     return ORBG_OK;
 }
 
@@ -467,14 +494,12 @@ int decode_single(const uint8_t* H, const float* llr, int n, int k, uint64_t bud
                                         st);
         }
     } else {
-        rc = describe(code, order && budget < 4096 ? 4096 : budget, st, 0, &a.codes.c[0]);
+        rc = describe(code, order && budget < 4096 ? 4096 : budget, budget, st, 0, &a.codes.c[0]);
     }
     if (rc) return rc;
     a.codes.rwords = a.codes.c[0].m * a.codes.c[0].nk;
     if (batch == 0) return ORBG_OK;
     a.p = resolve_params(params, order != nullptr);
-    Workspace* w = nullptr;
-    if ((rc = get_workspace(st, a.p.split_steps > 0 ? batch : 0, &w, &a.cus))) return rc;
     a.mixed = false;
     a.llr = llr;
     a.nblocks = batch;
@@ -485,8 +510,7 @@ int decode_single(const uint8_t* H, const float* llr, int n, int k, uint64_t bud
     a.cw = codeword;
     a.queries = queries;
     a.abandoned = abandoned;
-    a.ctrs = w->ctrs;
-    a.heavy = a.p.split_steps > 0 ? w->heavy : nullptr;
+    if ((rc = get_decode_space(st, &a))) return rc;
     const hipError_t e = orbg::launch_decode(a, st);
     if (e != hipSuccess) return fail(ORBG_EHIP, "decode launch failed: %s", hipGetErrorString(e));
     return ORBG_OK;
@@ -532,7 +556,7 @@ int decode_mixed(const int* codes, int ncodes, const uint8_t* block_code, const 
     a.codes.ncodes = ncodes;
     uint32_t col_base = 0, row_base = 0;
     for (int i = 0; i < ncodes; ++i) {
-        if ((rc = describe(list[i], budget, st, col_base, &a.codes.c[i], !noalloc))) return rc;
+        if ((rc = describe(list[i], budget, budget, st, col_base, &a.codes.c[i], !noalloc))) return rc;
         a.codes.c[i].row_base = row_base;
         col_base += (uint32_t)list[i]->n;
         row_base += (uint32_t)(a.codes.c[i].m * a.codes.c[i].nk);
@@ -548,11 +572,6 @@ int decode_mixed(const int* codes, int ncodes, const uint8_t* block_code, const 
         if ((rc = compute_units(dev, &a.cus))) return rc;
         a.ctrs = scr;
         a.heavy = a.p.split_steps > 0 ? reinterpret_cast<int64_t*>(scr + ORBG_CTR_WORDS) : nullptr;
-    } else {
-        Workspace* w = nullptr;
-        if ((rc = get_workspace(st, a.p.split_steps > 0 ? batch : 0, &w, &a.cus))) return rc;
-        a.ctrs = w->ctrs;
-        a.heavy = a.p.split_steps > 0 ? w->heavy : nullptr;
     }
     a.mixed = true;
     a.block_code = block_code;
@@ -565,6 +584,7 @@ int decode_mixed(const int* codes, int ncodes, const uint8_t* block_code, const 
     a.cw = codeword;
     a.queries = queries;
     a.abandoned = abandoned;
+    if (!noalloc && (rc = get_decode_space(st, &a))) return rc;
     const hipError_t e = orbg::launch_decode(a, st);
     if (e != hipSuccess) return fail(ORBG_EHIP, "mixed decode launch failed: %s", hipGetErrorString(e));
     return ORBG_OK;
@@ -774,7 +794,7 @@ int orbg_decode_learned(const uint8_t* H, const float* llr, int n, int k, uint64
     orbg::DecodeArgs a;
     std::memset(&a, 0, sizeof(a));
     a.codes.ncodes = 1;
-    if ((rc = describe(code, budget < 4096 ? 4096 : budget, st, 0, &a.codes.c[0]))) return rc;
+    if ((rc = describe(code, budget < 4096 ? 4096 : budget, budget, st, 0, &a.codes.c[0]))) return rc;
     a.codes.rwords = a.codes.c[0].m * a.codes.c[0].nk;
     Workspace* ws = nullptr;
     if ((rc = get_workspace(st, 0, &ws, &a.cus))) return rc;
@@ -782,6 +802,7 @@ int orbg_decode_learned(const uint8_t* H, const float* llr, int n, int k, uint64
     // 1. the first batch of the plain order for every block; the rest are listed
     a.p = resolve_params(params, false);
     a.p.split_steps = 1;
+    a.p.naive = 0;                                        // the pass counts the blocks it leaves
     a.llr = llr;
     a.nblocks = batch;
     a.budget = (uint32_t)budget;
@@ -789,8 +810,8 @@ int orbg_decode_learned(const uint8_t* H, const float* llr, int n, int k, uint64
     a.queries = queries;
     a.abandoned = abandoned;
     a.ctrs = ws->ctrs;
-    a.heavy = lw.list;
     a.list_only = true;
+    a.list = lw.list;
     hipError_t e = orbg::launch_decode(a, st);
     if (e != hipSuccess) return fail(ORBG_EHIP, "first-batch pass failed: %s", hipGetErrorString(e));
     unsigned long long count = 0;
@@ -810,14 +831,12 @@ int orbg_decode_learned(const uint8_t* H, const float* llr, int n, int k, uint64
     // which indexes the caller's arrays directly)
     orbg::DecodeArgs b = a;
     b.p = resolve_params(params, true);
-    if (b.p.split_steps > 0 && (rc = get_workspace(st, (int64_t)count, &ws, &b.cus))) return rc;
-    b.ctrs = ws->ctrs;
-    b.heavy = b.p.split_steps > 0 ? ws->heavy : nullptr;
     b.list_only = false;
     b.ids = lw.list;
     b.nblocks = (int64_t)count;
     b.order = lw.orders;
     b.skip0 = true;
+    if ((rc = get_decode_space(st, &b))) return rc;
     e = orbg::launch_decode(b, st);
     if (e != hipSuccess) return fail(ORBG_EHIP, "ordered pass failed: %s", hipGetErrorString(e));
     return ORBG_OK;

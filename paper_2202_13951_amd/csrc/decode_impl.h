@@ -544,8 +544,8 @@ __device__ __forceinline__ void entry_syndrome2(const BlockLds<S>& L, uint2 ea, 
 // received position of each flipped rank is wave-uniform: it goes into a
 // wave-uniform mask of the positions to flip (one 64-bit word per key), which
 // every lane applies once at the end.
-template <int NK, typename S, class LO>
-__device__ __forceinline__ void write_codeword(const bool (&ybit)[NK], const BlockLds<S>& L, uint32_t win_lo,
+template <int NK, class LDS, class LO>
+__device__ __forceinline__ void write_codeword(const bool (&ybit)[NK], const LDS& L, uint32_t win_lo,
                                                uint32_t win_hi, buf_t cw_row, const LO& lo)
 {
     const int lane = lane_id();
@@ -827,7 +827,7 @@ __device__ __forceinline__ bool light_block(
         found = (r == 1);
     }
 
-    write_codeword<NK, S>(ybit, L, win_lo, win_hi, cw_row, lo);
+    write_codeword<NK>(ybit, L, win_lo, win_hi, cw_row, lo);
     if constexpr (has_offs<LO>())
         write_result(q_out, ab_out, found ? q : budget, !found, lo.r);
     else
@@ -836,6 +836,10 @@ __device__ __forceinline__ bool light_block(
     return false;
 }
 
+// A block that is left goes to the heavy list or, without one, is marked in its
+// abandon flag, to be listed afterwards (increments of one list's counter take 8 to
+// 12 ns each, which is longer than a first pass takes for a block; only the few
+// blocks of a heavy pass go that way).
 template <int NK, bool ORDERED, typename S, bool ONELINE, bool PAIRS = false, class LO = NoOffs>
 __device__ __forceinline__ void light_one(const float (&x)[NK], const uint64_t (&hrow)[NK], uint32_t ordv,
                                           const CodeDesc& c, const S* cols, BlockLds<S>& L, int64_t b, int64_t row,
@@ -848,8 +852,12 @@ __device__ __forceinline__ void light_one(const float (&x)[NK], const uint64_t (
         make_buf(cw + (row >= 0 ? row : 0), row >= 0 ? (uint32_t)c.n : 0u), queries + b, abandoned + b, lazy,
         j0_out ? j0_out + b : nullptr, lo, t0);
     if (left && lane_id() == 0) {
-        const unsigned long long slot = atomicAdd(ctrs + ORBG_CTR_HEAVY_COUNT, 1ull);
-        heavy[slot] = b;
+        if (heavy == nullptr) {
+            abandoned[b] = ORBG_OPEN;
+        } else {
+            const unsigned long long slot = atomicAdd(ctrs + ORBG_CTR_HEAVY_COUNT, 1ull);
+            heavy[slot] = b;
+        }
     }
 }
 
@@ -1409,7 +1417,7 @@ __device__ __forceinline__ void heavy_block(const CodeDesc& c, const float* __re
             win_lo = uniform_u32(w.x);
             win_hi = uniform_u32(w.y);
         }
-        write_codeword<NK, S>(ybit, L, win_lo, win_hi, make_buf(cw_row, row_ok ? (uint32_t)n : 0u), NoOffs{});
+        write_codeword<NK>(ybit, L, win_lo, win_hi, make_buf(cw_row, row_ok ? (uint32_t)n : 0u), NoOffs{});
         write_result(q_out, ab_out, found ? q : budget, !found);
     }
     __syncthreads();
@@ -1528,7 +1536,7 @@ static hipError_t launch_all(const DecodeArgs& a, hipStream_t stream)
         chunk = (int)(c >= K ? c - c % K : c);
     }
     chunk = chunk > 64 ? 64 : chunk;                    // a chunk's blocks fit one 64-bit mask
-    const uint32_t split = (a.heavy != nullptr && a.p.split_steps > 0) ? (uint32_t)a.p.split_steps : 0u;
+    const uint32_t split = ((a.heavy != nullptr || a.list_only) && a.p.split_steps > 0) ? (uint32_t)a.p.split_steps : 0u;
     launch_light<NKMAX, ORDERED, S, MIXED, ONELINE>(a, wgs, chunk, split, stream);
     if (split && !a.list_only) {
         if (a.p.heavy_waves >= 16) launch_heavy_g<NKMAX, S, MIXED, 16, ONELINE>(a, split, stream);

@@ -1,0 +1,316 @@
+// First pass of a large batch for gfx950: query 1 for every block, the first
+// batch of 64 patterns for the others; a block that neither decides is marked
+// for the match search (match_impl.h).
+//
+// One wave takes groups of K rows (all K loads in flight together) and works on
+// them from registers: base syndrome by row parities; s0 = 0 is query 1 and is
+// written out.  For the others a threshold on |LLR| picks the 9 to 16 least
+// reliable bits; their keys go to a 16-key slot in LDS.  Four slots are sorted
+// at a time, one per row of 16 lanes (10 substeps for four blocks, lane
+// exchanges inside DPP rows), and each block's patterns are tested one per
+// lane: the ranks a lane's pattern flips are the same for every block, so its
+// LDS addresses are made once per kernel and a test is four reads and an XOR.
+// With c ranks known, the patterns of logistic weight <= c are tested.
+//
+// Bound: vector and scalar issue (each wave instruction holds a SIMD for four
+// cycles) beside the one read of every row.
+#pragma once
+#include "match_impl.h"
+
+namespace orbg {
+
+#define ORBG_FIRST_MIN 9         // fewest ranks a block goes on with
+#define ORBG_FIRST_N 12          // shorter codes go to the match search
+#define ORBG_FIRST_SLOTS 32      // staged blocks: at most 3 left over and 16 of one group (a power of two)
+#define ORBG_FIRST_ROW 20        // ranks 0..16 of a sorted block, padded
+
+template <int NK, typename S>
+struct FirstLds {
+    uint32_t key[ORBG_FIRST_SLOTS * 16];
+    S h[4 * ORBG_FIRST_ROW];             // columns by rank of four sorted blocks (rank 0: zero)
+    uint32_t pi[4 * ORBG_FIRST_ROW];     // their received indices (rank 0: none)
+};
+
+// Lane l of `reg` <- v (both wave-uniform).  (clang has no builtin for it; the
+// name is the intrinsic's.)
+__device__ int32_t writelane_i32(int32_t v, int32_t l, int32_t old) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ void writelane(uint32_t& reg, uint32_t v, uint32_t l)
+{
+    reg = (uint32_t)writelane_i32((int32_t)v, (int32_t)l, (int32_t)reg);
+}
+
+template <int NK, typename S, bool MIXED>
+__global__ void __launch_bounds__(ORBG_WAVE)
+first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int64_t* __restrict__ row_off,
+             const float* __restrict__ llr, int64_t nblocks, uint32_t budget, uint8_t* __restrict__ cw,
+             uint64_t* __restrict__ queries, uint8_t* __restrict__ abandoned, int64_t row_limit)
+{
+    extern __shared__ __align__(16) unsigned char orbg_dyn_lds[];
+    uint64_t* s_rows = reinterpret_cast<uint64_t*>(orbg_dyn_lds);
+    S* s_cols = reinterpret_cast<S*>(orbg_dyn_lds + (size_t)codes.rwords * sizeof(uint64_t));
+    __shared__ FirstLds<NK, S> L;
+    constexpr int IB = IndexBits<NK>::value;
+    constexpr int K = ScreenDepth<NK>::value;
+    constexpr bool HOIST = !MIXED && NK <= 4;
+    const int lane = lane_id();
+    for (int ci = 0; ci < (MIXED ? codes.ncodes : 1); ++ci) {
+        const CodeDesc& c = codes.c[ci];
+        for (int i = threadIdx.x; i < c.n; i += ORBG_WAVE) s_cols[c.col_base + i] = (S)c.cols[i];
+        for (int i = threadIdx.x; i < c.m * c.nk; i += ORBG_WAVE) s_rows[c.row_base + i] = c.rows[i];
+    }
+    if (lane < 4) {
+        L.h[lane * ORBG_FIRST_ROW] = 0;
+        L.pi[lane * ORBG_FIRST_ROW] = ~0u;
+    }
+    // this lane's pattern of the first batch (at most four ranks), its weight
+    uint32_t a[4] = {0, 0, 0, 0}, wpat = 0;
+    {
+        // (the same for every length from 12 up: the batch reaches rank 12)
+        int cp = 0;
+        while (MIXED && cp + 1 < codes.ncodes && codes.c[cp].n < ORBG_FIRST_N) ++cp;
+        const uint2 e = load_entry(codes.c[cp].sched, (uint32_t)lane);
+        uint32_t m = e.x & 0xffu, high = e.x >> 8;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t r = m != 0 ? (uint32_t)__builtin_ctz(m) + 1u : (high & 0xffu);
+            high = m != 0 ? high : high >> 8;
+            m &= m - 1;
+            a[k] = r;
+            wpat += r;
+        }
+    }
+    wave_lds_sync();
+    uint64_t hrow0[NK];
+    if (HOIST) load_hrows<NK>(s_rows, codes.c[0].m, hrow0);
+    LaneOffs<NK> lo = lane_offsets<NK>(MIXED ? NK * ORBG_WAVE : codes.c[0].n);
+
+    // staged blocks: slot k's values in lane k
+    uint32_t ylo[NK], yhi[NK], syn_lo = 0, syn_hi = 0, id_lo = 0, id_hi = 0, meta = 0;   // meta: ranks | code << 8
+#pragma unroll
+    for (int j = 0; j < NK; ++j) ylo[j] = yhi[j] = 0;
+    uint32_t head = 0, staged = 0;
+    float tau = 2.0f;                                     // threshold, carried from block to block
+
+    auto row_of = [&](int64_t b, int& ci) -> int64_t {
+        ci = 0;
+        if (!MIXED) return b * codes.c[0].n;
+        ci = (int)scalar_load_u8(block_code, b);
+        ci = ci < codes.ncodes ? ci : 0;                  // out-of-range indices read code 0
+        const int64_t row = scalar_load_i64(row_off, b);
+        return uniform_i64((row >= 0 && row <= row_limit - codes.c[ci].n) ? row : -1);
+    };
+    // codeword y, query count and flag of block b
+    auto write = [&](int64_t b, int ci, int64_t row, const uint64_t (&y)[NK], uint32_t q) {
+        const int n = codes.c[ci].n;
+        const buf_t cb = make_buf(cw + (row >= 0 ? row : 0), row >= 0 ? (uint32_t)n : 0u);
+#pragma unroll
+        for (int j = 0; j < NK; ++j)
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(__builtin_amdgcn_inverse_ballot_w64(y[j]) ? 1 : 0), cb, lo.c[j],
+                                                 0, 0);
+        write_result(queries + b, abandoned + b, q, false, lo.r);
+    };
+
+    // Sorts the `cnt` (1..4) oldest staged blocks and tests their patterns.
+    auto flush = [&](uint32_t cnt) {
+        const uint32_t sub = (uint32_t)lane >> 4, in = (uint32_t)lane & 15u;
+        const uint32_t slot = (head + sub) & (ORBG_FIRST_SLOTS - 1);
+        const uint32_t mt = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(slot * 4u), (int)meta);
+        const uint32_t known = sub < cnt ? mt & 0xffu : 0u;
+        wave_lds_sync();
+        uint32_t k1[1] = {in < known ? L.key[slot * 16u + in] : 0xffffffffu};
+        bitonic_stage32<1, 2, 8>(k1);
+        // the last stage ascending in every row
+        {
+            uint32_t p;
+            p = lane_xor<8>(k1[0]);
+            k1[0] = ((p < k1[0]) == lane_bit<0x00ff00ff00ff00ffull>()) ? p : k1[0];
+            p = lane_xor<4>(k1[0]);
+            k1[0] = ((p < k1[0]) == lane_bit<0x0f0f0f0f0f0f0f0full>()) ? p : k1[0];
+            p = lane_xor<2>(k1[0]);
+            k1[0] = ((p < k1[0]) == lane_bit<0x3333333333333333ull>()) ? p : k1[0];
+            p = lane_xor<1>(k1[0]);
+            k1[0] = ((p < k1[0]) == lane_bit<0x5555555555555555ull>()) ? p : k1[0];
+        }
+        const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)k1[0], 0x101, 0xF, 0xF, false);   // row_shl:1
+        const uint64_t ties = ballot(in + 1u < known && ((k1[0] ^ next) >> IB) == 0u);
+        const uint32_t idx = k1[0] & ((1u << IB) - 1u);
+        const uint32_t base = MIXED ? (uint32_t)codes.c[0].col_base : 0u;
+        uint32_t cb = base;
+        if (MIXED)
+            for (int ci = 1; ci < codes.ncodes; ++ci) cb = (mt >> 8) == (uint32_t)ci ? codes.c[ci].col_base : cb;
+        const S col = s_cols[in < known ? cb + idx : 0u];
+        L.h[sub * ORBG_FIRST_ROW + 1 + in] = in < known ? col : (S)0;
+        L.pi[sub * ORBG_FIRST_ROW + 1 + in] = in < known ? idx : ~0u;
+        wave_lds_sync();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if ((uint32_t)j >= cnt) break;
+            const int sl = (int)((head + j) & (ORBG_FIRST_SLOTS - 1));
+            const uint32_t info = (uint32_t)__builtin_amdgcn_readlane((int)meta, sl);
+            const S s0 = sizeof(S) == 4 ? (S)(uint32_t)__builtin_amdgcn_readlane((int)syn_lo, sl)
+                                        : (S)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)syn_hi, sl) << 32) |
+                                              (uint32_t)__builtin_amdgcn_readlane((int)syn_lo, sl));
+            const int64_t b = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)id_hi, sl) << 32) |
+                                        (uint32_t)__builtin_amdgcn_readlane((int)id_lo, sl));
+            const S* h = L.h + j * ORBG_FIRST_ROW;
+            const S v = xor3<S>(xor3<S>(s0, h[a[0]], h[a[1]]), h[a[2]], h[a[3]]);
+            const uint64_t hits = ballot(v == 0 && wpat <= (info & 0xffu));
+            const uint32_t wl = hits != 0 ? (uint32_t)__builtin_ctzll(hits) : 0u;
+            if (hits != 0 && ((ties >> (16 * j)) & 0xffffull) == 0ull && wl < budget) {
+                uint64_t y[NK];
+#pragma unroll
+                for (int k = 0; k < NK; ++k)
+                    y[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)yhi[k], sl) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)ylo[k], sl);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t p =
+                        (uint32_t)__builtin_amdgcn_readlane((int)L.pi[j * ORBG_FIRST_ROW + a[u]], (int)wl);
+#pragma unroll
+                    for (int k = 0; k < NK; ++k) y[k] ^= (p >> 6) == (uint32_t)k ? 1ull << (p & 63u) : 0ull;
+                }
+                int ci = 0;
+                const int64_t row = row_of(b, ci);
+                write(b, ci, row, y, wl + 1u);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)ORBG_OPEN, make_buf(abandoned + b, 1), lo.r, 0, 0);
+            }
+        }
+        wave_lds_sync();
+        head = (head + cnt) & (ORBG_FIRST_SLOTS - 1);
+        staged -= cnt;
+    };
+
+    const int64_t step = (int64_t)gridDim.x * K;
+    for (int64_t g = (int64_t)blockIdx.x * K; g < nblocks; g += step) {
+        float xs[K][NK];
+        int64_t rows[K];
+        int cis[K];
+        const uint32_t cnt = uniform_u32((uint32_t)(nblocks - g < K ? nblocks - g : K));
+        if constexpr (!MIXED) {
+            // the group's rows lie back to back: one descriptor, a scalar offset per row
+            const uint32_t n4 = (uint32_t)codes.c[0].n * 4u;
+            const buf_t lb = make_buf(llr + g * codes.c[0].n, cnt * n4);
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) load_row_buf<NK>(lb, xs[kk], lo, (uint32_t)kk < cnt ? (uint32_t)kk * n4 : 0u);
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) {
+                cis[kk] = 0;
+                rows[kk] = (uint32_t)kk < cnt ? row_of(g + kk, cis[kk]) : -1;
+                const bool rv = rows[kk] >= 0;
+                load_row_buf<NK>(make_buf(llr + (rv ? rows[kk] : 0), rv ? (uint32_t)codes.c[cis[kk]].n * 4u : 0u), xs[kk],
+                                 lo);
+            }
+        }
+        int64_t g2 = g;
+        uint32_t cnt2 = cnt;
+        asm volatile("" : "+s"(g2), "+s"(cnt2));          // (row values are made again after the loads)
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk) {
+            if ((uint32_t)kk >= cnt2) break;
+            const int ci = MIXED ? cis[kk] : 0;
+            const CodeDesc& c = codes.c[ci];
+            uint64_t hr[NK];
+            if (HOIST) {
+#pragma unroll
+                for (int j = 0; j < NK; ++j) hr[j] = hrow0[j];
+            } else {
+                load_hrows_pad<NK>(s_rows + c.row_base, c.m, c.nk, hr);
+            }
+            bool yb[NK];
+            const S s0 = hard_decision<NK, S>(xs[kk], c.n, hr, yb);
+            uint64_t y[NK];
+#pragma unroll
+            for (int j = 0; j < NK; ++j) y[j] = ballot(yb[j]);
+            if (s0 == 0) {
+                write(g2 + kk, ci, MIXED ? rows[kk] : (g2 + kk) * c.n, y, 1u);
+                continue;
+            }
+            // threshold: 9 to 16 magnitudes below it, by steps of a quarter and
+            // then by halves
+            uint32_t below = 0;
+            uint64_t mk[NK];
+            auto pick = [&]() {
+                below = 0;
+#pragma unroll
+                for (int j = 0; j < NK; ++j) {
+                    // lanes past n read 0 and are no candidates
+                    mk[j] = ballot(fabsf(xs[kk][j]) < tau) &
+                            (c.n >= (j + 1) * ORBG_WAVE ? ~0ull : c.n <= j * ORBG_WAVE ? 0ull
+                                                                                    : (1ull << (c.n & 63)) - 1ull);
+                    below += (uint32_t)__builtin_popcountll(mk[j]);
+                }
+            };
+            float lo_t = 0.0f, hi_t = 0.0f;               // bracket (0: open)
+            for (int it = 0; it < 8; ++it) {
+                pick();
+                if (below >= ORBG_FIRST_MIN && below <= 16u) break;
+                const bool up = below < ORBG_FIRST_MIN;
+                lo_t = up ? tau : lo_t;
+                hi_t = up ? hi_t : tau;
+                const float open = tau * (up ? 1.25f : 0.8f);
+                const float mid = 0.5f * (lo_t + hi_t);
+                tau = __uint_as_float(uniform_u32(__float_as_uint(lo_t == 0.0f || hi_t == 0.0f ? open : mid)));
+            }
+            if (below < ORBG_FIRST_MIN || below > 16u || c.n < ORBG_FIRST_N) {
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)ORBG_OPEN, make_buf(abandoned + g2 + kk, 1), lo.r, 0, 0);
+                continue;
+            }
+            const uint32_t slot = (head + staged) & (ORBG_FIRST_SLOTS - 1);
+            uint32_t at = slot * 16u;
+#pragma unroll
+            for (int j = 0; j < NK; ++j) {
+                const uint32_t i = (uint32_t)(j * ORBG_WAVE + lane);
+                // truncated magnitude above the index, as in rank_order
+                const uint32_t key = ((__float_as_uint(xs[kk][j]) & 0x7fffffffu) >> (IB - 1)) << IB | i;
+                const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(mk[j] >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mk[j], at));
+                if (__builtin_amdgcn_inverse_ballot_w64(mk[j])) L.key[to] = key;
+                at += (uint32_t)__builtin_popcountll(mk[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < NK; ++j) {
+                writelane(ylo[j], (uint32_t)y[j], slot);
+                writelane(yhi[j], (uint32_t)(y[j] >> 32), slot);
+            }
+            writelane(syn_lo, (uint32_t)s0, slot);
+            if (sizeof(S) == 8) writelane(syn_hi, (uint32_t)((uint64_t)s0 >> 32), slot);
+            writelane(id_lo, (uint32_t)(uint64_t)(g2 + kk), slot);
+            writelane(id_hi, (uint32_t)((uint64_t)(g2 + kk) >> 32), slot);
+            writelane(meta, below | ((uint32_t)ci << 8), slot);
+            ++staged;
+        }
+        while (staged >= 4u) flush(4u);
+    }
+    if (staged != 0) flush(staged);
+}
+
+template <int NK, typename S, bool MIXED>
+static hipError_t launch_first_as(const DecodeArgs& a, hipStream_t stream)
+{
+    uint32_t ncols = 0;
+    for (int i = 0; i < (MIXED ? a.codes.ncodes : 1); ++i) {
+        const uint32_t e = a.codes.c[i].col_base + (uint32_t)a.codes.c[i].n;
+        ncols = e > ncols ? e : ncols;
+    }
+    const size_t lds = (size_t)a.codes.rwords * sizeof(uint64_t) + ncols * sizeof(S);
+    const int64_t units = (a.nblocks + ScreenDepth<NK>::value - 1) / ScreenDepth<NK>::value;
+    const int64_t most = (int64_t)a.cus * 32;
+    first_kernel<NK, S, MIXED><<<(unsigned)(units < most ? units : most), ORBG_WAVE, lds, stream>>>(
+        a.codes, a.block_code, a.row_off, a.llr, a.nblocks, a.budget, a.cw, a.queries, a.abandoned, a.row_limit);
+    return hipGetLastError();
+}
+
+template <int NK>
+hipError_t launch_first_nk(const DecodeArgs& a, bool s32, hipStream_t stream)
+{
+    if (a.mixed) {
+        if constexpr (NK <= 4)
+            return s32 ? launch_first_as<NK, uint32_t, true>(a, stream) : launch_first_as<NK, uint64_t, true>(a, stream);
+        return hipErrorInvalidValue;                      // mixed launches take n <= 256
+    }
+    return s32 ? launch_first_as<NK, uint32_t, false>(a, stream) : launch_first_as<NK, uint64_t, false>(a, stream);
+}
+
+}  // namespace orbg

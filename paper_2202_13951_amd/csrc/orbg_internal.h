@@ -30,6 +30,21 @@ struct ClassInfo {
     uint64_t count;
 };
 
+// Tables of the match search (decode_impl.h, match_search): the sets of ranks
+// above 8 a pattern of the schedule can flip, and the counts that give a
+// pattern's position in the order.
+#define ORBG_MATCH_M 10      // fewest check bits of a code that uses it
+#define ORBG_MATCH_PAD 3     // batches of 64 end marks after the last set
+#define ORBG_MATCH_WCOL 104  // columns of the count tables: logistic weights 0..100, padded
+#define ORBG_MATCH_END 255   // logistic weight of an end mark (above every limit)
+struct MatchTable {
+    uint2* sets = nullptr;        // sets of at most 7 ranks in 9..n by (logistic weight, size): x = r1 r2 r3 r4
+                                  // and y = r5 r6 r7 weight as big-endian bytes (ranks ascending, 0 = none)
+    uint32_t* below = nullptr;    // below[w][W] = patterns of Hamming weight w (0..16) and logistic weight <= W
+    uint32_t* above = nullptr;    // above[c][r][s] = r-subsets (r < 16) of ranks c + 1 .. n with sum s, c = 0..100
+    uint64_t total[ORBG_WLEVEL_SCHED + 1];  // host: patterns of logistic weight <= W
+};
+
 // Device-resident query schedule for one (n, len).
 struct Schedule {
     int n;
@@ -40,6 +55,7 @@ struct Schedule {
     int rmax;           // largest rank any entry references
     int rmax0;          // largest rank an entry of the first batch of 64 references
     int wlast;          // logistic weight of the last entry
+    MatchTable match;   // empty for n <= 8
 };
 
 // 1-line ORBGRAND schedules for one (n, len): j0max + 2 schedules of `len`
@@ -56,6 +72,8 @@ struct Schedule1 {
 };
 
 int orbg_build_schedule(int n, uint64_t len, hipStream_t stream, Schedule* out, char* err, size_t errlen);
+// Match-search tables for patterns of logistic weight <= wlast (<= 100).
+int orbg_build_match(int n, int wlast, MatchTable* out, char* err, size_t errlen);
 int orbg_build_schedule_1line(int n, uint64_t len, hipStream_t stream, Schedule1* out, char* err, size_t errlen);
 // Unpacks `count` entries from `entries` to 16-byte lists of 1-based ranks.
 int orbg_unpack_entries(const uint2* entries, uint64_t count, uint8_t* d_out, hipStream_t stream);

@@ -21,6 +21,11 @@ struct CodeDesc {
     const uint64_t* cols;      // n packed parity-check columns
     const uint64_t* rows;      // m x nk packed parity-check rows (bit l of word j = H[r][64 j + l])
     const uint2* sched;        // schedule entries for this n (1-line: the schedule of offset -1)
+    const uint2* sets;         // match search: sets of ranks above 8, or nullptr (step search only)
+    const uint32_t* below;     // match search: count tables (MatchTable)
+    const uint32_t* above;
+    int wprefix;               // match search: logistic weight of query 4096
+    int wlim;                  // match search: logistic weight of the last query within the budget
     int j0max;                 // 1-line: largest offset with a schedule of its own
     uint32_t sstride;          // 1-line: entries between the schedules of consecutive offsets
 };
@@ -58,7 +63,8 @@ struct DecodeArgs {
     uint8_t* abandoned;
     unsigned long long* ctrs;  // device work counters (8 slices, heavy count, heavy next)
     int64_t* heavy;            // device heavy-block list, capacity >= nblocks when splitting
-    bool list_only;            // blocks left after split_steps are only listed in heavy (no heavy pass)
+    bool list_only;            // blocks left after split_steps are only listed (no heavy pass):
+    int64_t* list;             // in list (room for nblocks), their number in the heavy-block counter
     const int64_t* ids;        // device, nblocks: caller's block index of each position, or nullptr
                                // (one code, no heavy pass; the batch order stays per position)
     bool skip0;                // ordered decode of blocks known to hold no member in batch 0:
@@ -77,5 +83,18 @@ struct DecodeArgs {
 #define ORBG_CTR_WORDS ((ORBG_SLICES + 2) * 16)
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
+
+// A block left by a pass for the next one has this abandon flag in between.
+#define ORBG_OPEN 2
+
+// The match search decodes every code that has its tables, but not the 1-line
+// order, nor where the first batch alone or the naive launch is asked for.
+inline bool uses_match(const DecodeArgs& a)
+{
+    if (a.oneline || a.list_only || a.p.naive) return false;
+    for (int i = 0; i < a.codes.ncodes; ++i)
+        if (a.codes.c[i].sets == nullptr) return false;
+    return true;
+}
 
 }  // namespace orbg

@@ -257,6 +257,80 @@ int orbg_build_schedule(int n, uint64_t len, hipStream_t stream, Schedule* out, 
     out->rmax = rmax[0];
     out->rmax0 = rmax[1];
     out->wlast = host_small[1];
+    const int rc = n > ORBG_LOW_RANKS ? orbg_build_match(n, out->wlast, &out->match, err, errlen) : 0;
+    if (rc != 0) (void)hipFree(d_entries);
+    return rc;
+}
+
+// Every set is listed by a depth-first walk on the host (80 thousand sets for
+// the largest limit), sorted by a counting sort over (weight, size).
+int orbg_build_match(int n, int wlast, MatchTable* out, char* err, size_t errlen)
+{
+    const int WC = ORBG_MATCH_WCOL, RW = ORBG_WMAX_H + 1, top = n < ORBG_WLEVEL_SCHED ? n : ORBG_WLEVEL_SCHED;
+    const uint32_t cap = 1u << 24;                    // counts saturate above every budget
+    std::vector<uint64_t> keys;                       // ranks r1 .. r7 and the weight, big-endian
+    uint8_t v[ORBG_HIGH_SLOTS];
+    auto walk = [&](auto&& self, int depth, int from, int weight) -> void {
+        uint64_t e = 0;
+        for (int i = 0; i < ORBG_HIGH_SLOTS; ++i) e = (e << 8) | (i < depth ? v[i] : 0u);
+        keys.push_back((e << 8) | (uint64_t)weight);
+        if (depth == ORBG_HIGH_SLOTS) return;
+        for (int r = from; r <= n && weight + r <= wlast; ++r) {
+            v[depth] = (uint8_t)r;
+            self(self, depth + 1, r + 1, weight + r);
+        }
+    };
+    walk(walk, 0, ORBG_LOW_RANKS + 1, 0);
+    auto size_of = [](uint64_t e) {
+        int c = 0;
+        for (int i = 1; i <= ORBG_HIGH_SLOTS; ++i) c += ((e >> (8 * i)) & 0xffu) != 0;
+        return c;
+    };
+    std::vector<size_t> start((size_t)(wlast + 1) * 8 + 1, 0);
+    for (uint64_t e : keys) ++start[(size_t)(e & 0xffu) * 8 + size_of(e) + 1];
+    for (size_t i = 1; i < start.size(); ++i) start[i] += start[i - 1];
+    const size_t padded = ((keys.size() + 63) / 64 + ORBG_MATCH_PAD) * 64;
+    std::vector<uint2> sets(padded, make_uint2(0u, (uint32_t)ORBG_MATCH_END));
+    for (uint64_t e : keys) sets[start[(size_t)(e & 0xffu) * 8 + size_of(e)]++] = make_uint2((uint32_t)(e >> 32), (uint32_t)e);
+    // counts of subsets of {c + 1 .. n} by size and sum, c from the top down
+    std::vector<uint32_t> above((size_t)(ORBG_WLEVEL_SCHED + 1) * 16 * WC, 0u);
+    std::vector<uint64_t> cnt((size_t)RW * WC, 0ull);
+    cnt[0] = 1;
+    for (int c = ORBG_WLEVEL_SCHED; c >= 0; --c) {
+        if (c < top)                                   // rank c + 1 joins
+            for (int r = ORBG_WMAX_H; r >= 1; --r)
+                for (int s = ORBG_WLEVEL_SCHED; s >= c + 1; --s) cnt[r * WC + s] += cnt[(r - 1) * WC + s - (c + 1)];
+        for (int r = 0; r < 16; ++r)
+            for (int s = 0; s <= ORBG_WLEVEL_SCHED; ++s)
+                above[((size_t)c * 16 + r) * WC + s] = (uint32_t)std::min<uint64_t>(cnt[r * WC + s], cap);
+    }
+    // cnt now counts the subsets of all ranks
+    std::vector<uint32_t> below((size_t)RW * WC, 0u);
+    for (int r = 0; r < RW; ++r) {
+        uint64_t sum = 0;
+        for (int s = 0; s <= ORBG_WLEVEL_SCHED; ++s) {
+            sum += cnt[r * WC + s];
+            below[r * WC + s] = (uint32_t)std::min<uint64_t>(sum, cap);
+        }
+    }
+    uint64_t all = 0;
+    for (int s = 0; s <= ORBG_WLEVEL_SCHED; ++s) {
+        for (int r = 0; r < RW; ++r) all += cnt[r * WC + s];
+        out->total[s] = all;
+    }
+    auto put = [](auto** d, const auto& h) {
+        return hipMalloc(d, h.size() * sizeof(h[0])) == hipSuccess &&
+               hipMemcpy(*d, h.data(), h.size() * sizeof(h[0]), hipMemcpyHostToDevice) == hipSuccess;
+    };
+    if (!put(&out->sets, sets) || !put(&out->below, below) || !put(&out->above, above)) {
+        snprintf(err, errlen, "schedule: cannot place the match-search tables (%zu sets)", keys.size());
+        (void)hipFree(out->sets);
+        (void)hipFree(out->below);
+        (void)hipFree(out->above);
+        out->sets = nullptr;
+        out->below = out->above = nullptr;
+        return -2;
+    }
     return 0;
 }
 

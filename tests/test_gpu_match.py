@@ -1,0 +1,121 @@
+"""GPU parity of the match search and its first pass (match_impl.h, first_impl.h)
+against the CPU oracle, bit for bit, where they can go wrong: the fewest check
+bits, every keys-per-lane width with ragged lengths, dependent columns among
+the least reliable ranks, tied magnitudes, budgets around the first batch and
+the reordered prefix, both sides of the one-launch batch size."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2202_13951_amd import binding
+from synth import channel, codes
+
+pytestmark = pytest.mark.gpu
+THREADS = min(16, os.cpu_count() or 1)
+DIRECT = 16384                       # largest batch decoded by one launch
+
+
+def _check(got, want, tag):
+    cw, q, ab = (t.cpu().numpy() for t in got)
+    bad = np.nonzero((cw != want[0]).any(axis=1) | (q.astype(np.uint64) != want[1]) | (ab != want[2]))[0]
+    assert bad.size == 0, f"{tag}: {bad.size} differ, first {bad[:8].tolist()}: gpu {q[bad[:4]]} oracle {want[1][bad[:4]]}"
+
+
+@pytest.mark.parametrize("n,m,blocks,ebn0,budget", [
+    (11, 10, 400, 2.0, 2048), (12, 10, DIRECT + 9, 3.0, 4096), (40, 10, DIRECT + 1, 4.0, 3000),
+    (64, 33, DIRECT + 63, 4.0, 300), (65, 11, DIRECT, 4.0, 2000), (128, 64, DIRECT + 7, 4.0, 100),
+    (129, 24, DIRECT + 5, 4.5, 700), (257, 20, DIRECT + 1, 5.5, 1000), (513, 22, DIRECT + 3, 6.0, 300),
+    (1024, 40, 300, 5.5, 20000)])
+def test_widths_and_batch_sizes(gpu_device, n, m, blocks, ebn0, budget):
+    print(f"match n={n} m={m} blocks={blocks}", flush=True)
+    H = codes.rlc_H(n, n - m, seed=n + m)
+    llr, _ = channel.awgn_llr(codes.generator_matrix(H), blocks, ebn0, seed=n * m)
+    got = binding.orbg_decode(H, torch.from_numpy(llr).to(gpu_device), budget)
+    _check(got, O.decode(H, llr, budget, THREADS), f"n={n} m={m}")
+
+
+@pytest.mark.parametrize("budget", [1, 2, 63, 64, 65, 8191])
+@pytest.mark.parametrize("blocks", [500, DIRECT + 2])
+def test_dependent_columns_and_ties(gpu_device, blocks, budget):
+    """Columns from a handful of values and zero columns, so that the eight least
+    reliable ranks hold one to eight null combinations; magnitudes on a coarse
+    grid in half of the blocks, so that ranks tie."""
+    print(f"match dependent blocks={blocks} budget={budget}", flush=True)
+    rng = np.random.default_rng(7)
+    n, m = 100, 12
+    pool = rng.integers(0, 2, size=(m, 9), dtype=np.uint8)
+    pool[:, 0] = 0
+    H = pool[:, rng.integers(0, 9, size=n)]
+    H[:, :m] = np.eye(m, dtype=np.uint8)
+    llr = (rng.standard_normal((blocks, n)) * 3).astype(np.float32)
+    llr[::2] = np.round(llr[::2] * 2) / 2
+    got = binding.orbg_decode(H, torch.from_numpy(llr).to(gpu_device), budget)
+    _check(got, O.decode(H, llr, budget, THREADS), f"dependent {blocks} {budget}")
+
+
+@pytest.mark.parametrize("budget", [64, 1000, 4096, 4097, 30000])
+def test_batch_orders_that_repeat_or_leave_out_batches(gpu_device, budget):
+    """A batch order is any 64 bytes (taken modulo 64): batches it leaves out are
+    not tested, a repeated one counts again.  The expected results come from the
+    oracle's pattern order, pattern by pattern."""
+    print(f"match order budget={budget}", flush=True)
+    rng = np.random.default_rng(budget)
+    n, m, N = 90, 14, 150
+    H = codes.rlc_H(n, n - m, seed=3)
+    llr, _ = channel.awgn_llr(codes.generator_matrix(H), N, 3.0, seed=11)
+    order = np.stack([rng.permutation(64) for _ in range(N)]).astype(np.uint8)
+    order[::3, rng.integers(0, 64, 20)] = rng.integers(0, 64, 20)
+    order[1::3] += 64 * rng.integers(0, 4, 64, dtype=np.uint8)
+    got = binding.orbg_decode_ordered(H, torch.from_numpy(llr).to(gpu_device), budget,
+                                      torch.from_numpy(order).to(gpu_device))
+    pats = O.order_prefix_array(n, max(budget, 4096))
+    cols = (H.astype(np.int64) << np.arange(m)[:, None]).sum(0)
+    cw = (llr > 0).astype(np.uint8)
+    q, ab = np.full(N, budget, dtype=np.uint64), np.ones(N, dtype=np.uint8)
+    for b in range(N):
+        perm = np.argsort(np.abs(llr[b]), kind="stable")
+        h = np.concatenate([[0], cols[perm]])
+        syn = np.bitwise_xor.reduce(cols * cw[b])
+        member = np.bitwise_xor.reduce(h[pats], axis=1) == syn
+        seq = np.concatenate([(order[b].astype(np.int64)[:, None] % 64 * 64 + np.arange(64)).reshape(-1),
+                              np.arange(4096, len(pats))])[:budget]
+        hit = np.nonzero(member[seq])[0]
+        if hit.size:
+            q[b], ab[b] = hit[0] + 1, 0
+            ranks = pats[seq[hit[0]]]
+            cw[b, perm[ranks[ranks > 0] - 1]] ^= 1
+    _check(got, (cw, q, ab), f"order {budget}")
+
+
+def test_mixed_codes_through_both_passes(gpu_device):
+    """Five codes of three widths, one too short for the first pass, in one batch."""
+    print("match mixed", flush=True)
+    rng = np.random.default_rng(5)
+    specs = [(11, 10), (64, 14), (100, 15), (127, 40), (250, 18)]
+    Hs = [codes.rlc_H(n, n - m, seed=n) for n, m in specs]
+    rows = []
+    for H in Hs:
+        llr, _ = channel.awgn_llr(codes.generator_matrix(H), 4000, 4.0, seed=H.shape[1])
+        rows.append(llr)
+    which = rng.permutation(np.repeat(np.arange(5), 4000)).astype(np.uint8)
+    lens = np.array([n for n, _ in specs])[which]
+    off = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int64)
+    flat = np.empty(int(lens.sum()), dtype=np.float32)
+    at = [np.nonzero(which == i)[0] for i in range(5)]
+    for i, (n, _) in enumerate(specs):
+        flat[(off[at[i]][:, None] + np.arange(n)).reshape(-1)] = rows[i].reshape(-1)
+    dev = gpu_device
+    ids = [binding.orbg_code_register(H) for H in Hs]
+    cw = torch.zeros(flat.size, dtype=torch.uint8, device=dev)
+    q = torch.zeros(which.size, dtype=torch.int64, device=dev)
+    ab = torch.zeros(which.size, dtype=torch.uint8, device=dev)
+    binding.orbg_decode_mixed(ids, torch.from_numpy(which).to(dev), torch.from_numpy(off).to(dev),
+                              torch.from_numpy(flat).to(dev), 2000, cw, q, ab)
+    cw, q, ab = cw.cpu(), q.cpu(), ab.cpu()
+    for i, (n, _) in enumerate(specs):
+        idx = torch.from_numpy(off[at[i]])[:, None] + torch.arange(n)
+        want = O.decode(Hs[i], rows[i], 2000, THREADS)
+        _check((cw[idx], q[at[i]], ab[at[i]]), want, f"mixed n={n}")
