@@ -168,6 +168,8 @@ DECODE_SOURCES = ("decode.hip", "decode_impl.h", "decode_nk1.hip", "decode_nk2.h
                   "decode_nk16.hip", "match_impl.h", "first_impl.h", "match_nk1.hip", "match_nk2.hip", "match_nk4.hip",
                   "match_nk8.hip", "match_nk16.hip", "orbg_device.h", "orbg_internal.h", "orbg_kernels.h", "schedule.hip")
 MLINE_SOURCES = ("mline.hip", "mline_impl.h", "mline_m1.hip", "mline_m2.hip", "mline_m3.hip", "mline_m4.hip", "orbg_mline.h",
+                 "mline_match_impl.h", "mline_match_nk1.hip", "mline_match_nk2.hip", "mline_match_nk4.hip", "mline_match_nk8.hip",
+                 "match_impl.h", "decode_impl.h",
                  "orbg_device.h", "orbg_internal.h")
 
 

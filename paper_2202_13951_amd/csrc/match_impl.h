@@ -26,7 +26,6 @@
 
 namespace orbg {
 
-#define ORBG_MATCH_RANKS 128     // ranks whose columns the search can hold (it reaches 100)
 #define ORBG_MATCH_SOME 44       // fewest ranks of a partial ranking (at most 64), where the limit needs as many
 
 template <typename S>

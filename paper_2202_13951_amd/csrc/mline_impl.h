@@ -53,6 +53,7 @@
 #include "orbg_device.h"
 #include "orbg_internal.h"
 #include "orbg_mline.h"
+#include "mline_match_impl.h"
 
 namespace orbg {
 
@@ -1042,14 +1043,19 @@ __device__ __forceinline__ void decode_walk(const Model& md, const uint32_t* tbl
 template <int NK, int MM>
 __global__ void __launch_bounds__(ORBG_WAVE) __attribute__((amdgpu_waves_per_eu(NK <= 2 ? 5 : 1))) mline_kernel(MlineArgs a)
 {
-    __shared__ MlLds<NK * ORBG_WAVE> S;
+    __shared__ union {
+        MlLds<NK * ORBG_WAVE> walk;
+        MmLds<NK, uint64_t, true> match;
+    } lds;
+    auto& S = lds.walk;
     const int lane = lane_id();
     const int n = a.n;
     // rows of H, one per lane (lanes >= n - k hold zeros)
     uint64_t hrow[NK];
 #pragma unroll
     for (int j = 0; j < NK; ++j) hrow[j] = lane < a.m ? a.rows[lane * NK + j] : 0ull;
-    for (int64_t b = blockIdx.x; b < a.nblocks; b += gridDim.x) {
+    BlockCursor cur(a.marked ? a.abandoned : nullptr, a.nblocks, ORBG_WAVE);
+    for (int64_t b = cur.next(); b >= 0; b = cur.next()) {
         const float* row = a.llr + b * (int64_t)n;
         float x[NK];
         bool ybit[NK];
@@ -1062,6 +1068,8 @@ __global__ void __launch_bounds__(ORBG_WAVE) __attribute__((amdgpu_waves_per_eu(
             const uint64_t y = ballot(ybit[j]);
             acc += __popcll(hrow[j] & y);
         }
+        // a block that the first search left for its large weights
+        if (a.marked && mline_match_block<NK, uint64_t, true>(a, a.sets, lds.match, x, hrow, b) != 0) continue;
         const uint64_t s0 = uniform_u64(ballot((acc & 1u) != 0u));
         bool found = false;
         uint32_t q = a.budget;

@@ -1,0 +1,6 @@
+// m-line match-search kernel with 4 keys per lane (codes with n <= 256).
+#include "mline_match_impl.h"
+
+namespace orbg {
+template hipError_t launch_mline_match_nk<4>(const MlineArgs& a, int grid, hipStream_t stream);
+}  // namespace orbg

@@ -13,6 +13,20 @@
 
 namespace orbg {
 
+// Sets of ranks above 8 for the match search (mline_match_impl.h): list c holds
+// the sets of c ranks in 9 .. min(n, 254) by ascending rank sum, as in
+// MatchTable::sets without the weight byte, then two steps of end marks (the
+// rank after the last: 129 or 255).  Lists of three ranks and more are cut to about ORBG_MM_LIST sets.
+#define ORBG_MM_RANKS 254
+#define ORBG_MM_SUMS 1800        // rank sums (seven ranks of at most 254 reach 1757)
+#define ORBG_MM_LIST (1 << 19)
+struct MlineSets {
+    const uint2* sets;         // device
+    const uint32_t* end;       // device: end[c][s] = sets of list c of rank sum <= s
+    const int* limit;          // device: limit[c] = list c holds every set of rank sum <= limit[c]
+    uint32_t start[8];         // first entry of each list
+};
+
 struct MlineArgs {
     const float* llr;          // nblocks x n
     int n;
@@ -29,6 +43,8 @@ struct MlineArgs {
     uint8_t* abandoned;
     int32_t* mfit;             // per-block segment count, or nullptr
     int32_t* j0;               // per-block J_0 of the fit (the 1-line offset for one segment), or nullptr
+    MlineSets sets;            // match search
+    bool marked;               // only the blocks that the match search left (marked in abandoned)
 };
 
 // Entries of the subset-count table: (LMAX + 1) x (WMAX + 1) x SMAX.
@@ -36,6 +52,12 @@ constexpr size_t subset_table_words() { return (size_t)(ORBG_ML_LMAX + 1) * (ORB
 
 hipError_t build_subset_table(uint32_t* t, hipStream_t stream);
 hipError_t launch_mline(const MlineArgs& a, int grid, hipStream_t stream);
+template <int NK>
+hipError_t launch_mline_match_nk(const MlineArgs& a, int grid, hipStream_t stream);
+extern template hipError_t launch_mline_match_nk<1>(const MlineArgs&, int, hipStream_t);
+extern template hipError_t launch_mline_match_nk<2>(const MlineArgs&, int, hipStream_t);
+extern template hipError_t launch_mline_match_nk<4>(const MlineArgs&, int, hipStream_t);
+extern template hipError_t launch_mline_match_nk<8>(const MlineArgs&, int, hipStream_t);
 // The kernels for fits of at most MM segments (one translation unit each).
 template <int MM>
 hipError_t launch_mline_m(const MlineArgs& a, int grid, hipStream_t stream);

@@ -119,3 +119,40 @@ def test_mixed_codes_through_both_passes(gpu_device):
         idx = torch.from_numpy(off[at[i]])[:, None] + torch.arange(n)
         want = O.decode(Hs[i], rows[i], 2000, THREADS)
         _check((cw[idx], q[at[i]], ab[at[i]]), want, f"mixed n={n}")
+
+
+@pytest.mark.parametrize("n,m,segments", [(9, 5, 1), (66, 30, 2), (200, 40, 4), (256, 20, 1), (300, 22, 3), (512, 20, 2)])
+@pytest.mark.parametrize("curve", ["offset", "flat start", "steep start", "awgn"])
+def test_mline_curves(gpu_device, n, m, segments, curve):
+    """Magnitude curves that send the m-line match search through its parts: a
+    large offset (every single rank before any pair, ranks past 254 among them),
+    a nearly flat first segment (weights past the narrow tables, some past the
+    wide ones), a steep one (offsets of the later segments below the first's
+    end), and channel blocks; words at distance 1 to 4 from a codeword.  Every
+    curve is noisy: on one that is linear to rounding the gaps of the fit are
+    rounding errors, and the library evaluates its lines with one rounding less
+    than the oracle."""
+    print(f"mline curve {curve} n={n} m={m} segments={segments}", flush=True)
+    rng = np.random.default_rng(n + len(curve))
+    H = codes.rlc_H(n, n - m, seed=n)
+    G = codes.generator_matrix(H)
+    N = 64
+    if curve == "awgn":
+        llr, _ = channel.awgn_llr(G, N, 4.5, seed=n)
+    else:
+        r = np.arange(n, dtype=np.float64)
+        mags = {"offset": 10.0 + 0.01 * r, "steep start": np.where(r < n // 8, 1.0 + r, 1.0 + n // 8 + 0.05 * (r - n // 8)),
+                "flat start": np.where(r < max(3, n // 10), 0.5 + 1e-4 * r, 0.5 + 0.2 * (r - max(3, n // 10) + 1))}[curve]
+        cw = channel.encode(G, rng.integers(0, 2, size=(N, G.shape[0]), dtype=np.uint8))
+        llr = np.empty((N, n), dtype=np.float32)
+        for b in range(N):
+            perm = rng.permutation(n)
+            rx = cw[b].copy()
+            reach = n if b % 2 else max(4, n // 8)
+            rx[perm[rng.choice(reach, size=1 + b % min(4, reach), replace=False)]] ^= 1
+            llr[b, perm] = (mags * (1 + 1e-3 * (1 + b % 5) * rng.standard_normal(n))).astype(np.float32) * (2.0 * rx[perm] - 1)
+    budget = min(40000, 2 ** n)
+    got = binding.orbg_decode_mline(H, torch.from_numpy(llr).to(gpu_device), budget, segments)
+    want = O.decode_mline(H, llr, budget, segments, threads=THREADS)
+    _check(got[:3], want[:3], f"mline {curve} n={n}")
+    assert (got[3].cpu().numpy() == want[3]).all()
