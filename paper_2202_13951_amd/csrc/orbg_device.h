@@ -209,4 +209,102 @@ __device__ __forceinline__ void bitonic_sort32_groups(uint32_t (&key)[1])
     bitonic_stage32<1, 2, GROUP>(key);
 }
 
+// Ascending sorts of several short sequences at once: groups of LG consecutive
+// lanes (8 or 16) hold one sequence of LG R keys each, element e of it in
+// register e % R of its lane e / R.  Bitonic network with mirrored first
+// substeps, so every compare-exchange puts the smaller key at the lower index:
+// inside a lane it is a minimum and a maximum without a select.  OP: MIN and MAX
+// of two registers (32-bit keys, or two independent 16-bit keys per register).
+struct KeyU32 {
+    static __device__ __forceinline__ uint32_t min(uint32_t a, uint32_t b) { return a < b ? a : b; }
+    static __device__ __forceinline__ uint32_t max(uint32_t a, uint32_t b) { return a < b ? b : a; }
+};
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+struct KeyPairU16 {
+    static __device__ __forceinline__ uint32_t min(uint32_t a, uint32_t b)
+    {
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a),
+                                                                      __builtin_bit_cast(u16x2_t, b)));
+    }
+    static __device__ __forceinline__ uint32_t max(uint32_t a, uint32_t b)
+    {
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a),
+                                                                      __builtin_bit_cast(u16x2_t, b)));
+    }
+};
+
+// Value of lane (lane XOR M), all lanes active.
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor_mask(uint32_t v)
+{
+    if constexpr (M == 3) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x1B, 0xF, 0xF, false);     // quad_perm [3,2,1,0]
+    else if constexpr (M == 7) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);   // row_half_mirror
+    else if constexpr (M == 15) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);  // row_mirror
+    else return lane_xor<M>(v);
+}
+
+// Lanes that hold the lower index of an exchange over lane mask M.
+template <int M>
+constexpr uint64_t lower_lanes()
+{
+    const int top = M >= 8 ? 8 : M >= 4 ? 4 : M >= 2 ? 2 : 1;
+    uint64_t m = 0;
+    for (int l = 0; l < 64; ++l)
+        if ((l & top) == 0) m |= 1ull << l;
+    return m;
+}
+
+template <class OP, int R, int D>
+__device__ __forceinline__ void group_halves(uint32_t (&k)[R])
+{
+    if constexpr (D >= R) {
+        constexpr int M = D / R;
+        const bool low = lane_bit<lower_lanes<M>()>();
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const uint32_t p = lane_xor_mask<M>(k[j]);
+            const uint32_t a = OP::min(p, k[j]), b = OP::max(p, k[j]);
+            k[j] = low ? a : b;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if ((j & D) == 0) {
+                const uint32_t a = OP::min(k[j], k[j | D]), b = OP::max(k[j], k[j | D]);
+                k[j] = a;
+                k[j | D] = b;
+            }
+    }
+    if constexpr (D > 1) group_halves<OP, R, D / 2>(k);
+}
+
+template <class OP, int LG, int R, int SIZE = 2>
+__device__ __forceinline__ void group_sort(uint32_t (&k)[R])
+{
+    if constexpr (SIZE <= R) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int o = j ^ (SIZE - 1);
+            if (j < o) {
+                const uint32_t a = OP::min(k[j], k[o]), b = OP::max(k[j], k[o]);
+                k[j] = a;
+                k[o] = b;
+            }
+        }
+    } else {
+        constexpr int M = SIZE / R - 1;
+        const bool low = lane_bit<lower_lanes<M>()>();
+#pragma unroll
+        for (int j = 0; j < R / 2; ++j) {
+            const uint32_t p = lane_xor_mask<M>(k[R - 1 - j]), q = lane_xor_mask<M>(k[j]);
+            const uint32_t a = OP::min(p, k[j]), b = OP::max(p, k[j]);
+            const uint32_t c = OP::min(q, k[R - 1 - j]), d = OP::max(q, k[R - 1 - j]);
+            k[j] = low ? a : b;
+            k[R - 1 - j] = low ? c : d;
+        }
+    }
+    if constexpr (SIZE > 2) group_halves<OP, R, SIZE / 4>(k);
+    if constexpr (SIZE < LG * R) group_sort<OP, LG, R, SIZE * 2>(k);
+}
+
 }  // namespace orbg

@@ -19,21 +19,25 @@
 #define MLP_T_W2 (MLP_T_W1 + MLP_IN * MLP_HID)
 #define MLP_T_W3 (MLP_T_W2 + MLP_HID * MLP_HID)
 #define MLP_NTRANS (MLP_T_W3 + MLP_HID * MLP_OUT)
-#define MLP_KCHUNK_MIN 256   // fewest batch rows per split of a weight-gradient GEMM
-#define MLP_SPLITS_MAX 64    // most splits of a weight-gradient GEMM
+#define MLP_KCHUNK_MIN 512   // fewest batch rows per split of a weight gradient
+#define MLP_SPLITS_MAX 32    // most splits of a weight gradient
 #define MLP_BATCH_MAX (1 << 20)
 
 namespace orbg {
 
+// Work space of a training step: BF16 copies [feature][ldb] of a minibatch's
+// features, activations and gradients, FP32 partials and losses.
 struct MlpWorkspace {
-    uint16_t* h1;
-    uint16_t* h2;
-    float* logits;
-    uint16_t* dl;
-    uint16_t* dz2;
-    uint16_t* dz1;
-    float* part;
-    float* rowloss;
+    int64_t rows;            // the batch padded to a multiple of 32
+    int64_t ldb;             // row length of the copies (at least rows)
+    uint16_t* xt;
+    uint16_t* h1t;
+    uint16_t* h2t;
+    uint16_t* dlt;
+    uint16_t* dz2t;
+    uint16_t* dz1t;
+    float* part;             // splits x MLP_NPARAM
+    float* wloss;            // per wave of the first kernel: the loss of its rows
     int splits;              // batch rows split into `splits` chunks of `kchunk` (a multiple of 32)
     int kchunk;
     int64_t bytes;
