@@ -314,9 +314,7 @@ int describe(const CodeEntry* c, uint64_t need, uint64_t budget, hipStream_t st,
     d->rows = c->d_rows;
     d->row_base = 0;
     d->sched = s->entries;
-    // match search: codes with at least ORBG_MATCH_M check bits (fewer, and a
-    // search ends within a few steps: 2^m patterns hold a member on average)
-    if (s->match.sets != nullptr && d->m >= ORBG_MATCH_M) {
+    if (s->match.sets != nullptr) {
         d->sets = s->match.sets;
         d->below = s->match.below;
         d->above = s->match.above;

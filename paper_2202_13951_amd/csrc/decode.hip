@@ -116,8 +116,8 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream)
         }
         return e;
     }
-    // a batch order or a small batch: one launch
-    if (a.order || a.nblocks <= ORBG_MATCH_DIRECT) return launch_match(a, nk, s32, false, stream);
+    // a batch order, or a small batch whose searches are long enough: one launch
+    if (a.order || (a.nblocks <= ORBG_MATCH_DIRECT && many_checks(a))) return launch_match(a, nk, s32, false, stream);
     // else a first pass (screening and the first batch of patterns), then the
     // match search of the blocks it leaves
     const hipError_t e = launch_first(a, nk, s32, stream);

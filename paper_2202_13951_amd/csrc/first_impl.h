@@ -39,7 +39,8 @@ __device__ __forceinline__ void writelane(uint32_t& reg, uint32_t v, uint32_t l)
     reg = (uint32_t)writelane_i32((int32_t)v, (int32_t)l, (int32_t)reg);
 }
 
-template <int NK, typename S, bool MIXED>
+// K: rows per group (at most 16).
+template <int NK, typename S, bool MIXED, int K>
 __global__ void __launch_bounds__(ORBG_WAVE)
 first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int64_t* __restrict__ row_off,
              const float* __restrict__ llr, int64_t nblocks, uint32_t budget, uint8_t* __restrict__ cw,
@@ -50,7 +51,6 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     S* s_cols = reinterpret_cast<S*>(orbg_dyn_lds + (size_t)codes.rwords * sizeof(uint64_t));
     __shared__ FirstLds<NK, S> L;
     constexpr int IB = IndexBits<NK>::value;
-    constexpr int K = ScreenDepth<NK>::value;
     constexpr bool HOIST = !MIXED && NK <= 4;
     const int lane = lane_id();
     for (int ci = 0; ci < (MIXED ? codes.ncodes : 1); ++ci) {
@@ -295,11 +295,17 @@ static hipError_t launch_first_as(const DecodeArgs& a, hipStream_t stream)
         ncols = e > ncols ? e : ncols;
     }
     const size_t lds = (size_t)a.codes.rwords * sizeof(uint64_t) + ncols * sizeof(S);
-    const int64_t units = (a.nblocks + ScreenDepth<NK>::value - 1) / ScreenDepth<NK>::value;
+    // small batches: short groups, so that more waves share the rows
+    constexpr int KS = ScreenDepth<NK>::value < 4 ? ScreenDepth<NK>::value : 4;
     const int64_t most = (int64_t)a.cus * 32;
-    first_kernel<NK, S, MIXED><<<(unsigned)(units < most ? units : most), ORBG_WAVE, lds, stream>>>(
-        a.codes, a.block_code, a.row_off, a.llr, a.nblocks, a.budget, a.cw, a.queries, a.abandoned, a.row_limit);
-    return hipGetLastError();
+    auto go = [&](auto kernel, int k) {
+        const int64_t units = (a.nblocks + k - 1) / k;
+        kernel<<<(unsigned)(units < most ? units : most), ORBG_WAVE, lds, stream>>>(
+            a.codes, a.block_code, a.row_off, a.llr, a.nblocks, a.budget, a.cw, a.queries, a.abandoned, a.row_limit);
+        return hipGetLastError();
+    };
+    if (a.nblocks < most * ScreenDepth<NK>::value) return go(first_kernel<NK, S, MIXED, KS>, KS);
+    return go(first_kernel<NK, S, MIXED, ScreenDepth<NK>::value>, ScreenDepth<NK>::value);
 }
 
 template <int NK>

@@ -34,7 +34,6 @@ struct ClassInfo {
 // above 8 a pattern of the schedule can flip, and the counts that give a
 // pattern's position in the order.
 #define ORBG_MATCH_RANKS 128 // ranks whose columns a match search can hold
-#define ORBG_MATCH_M 10      // fewest check bits of a code that uses it
 #define ORBG_MATCH_PAD 3     // batches of 64 end marks after the last set
 #define ORBG_MATCH_WCOL 104  // columns of the count tables: logistic weights 0..100, padded
 #define ORBG_MATCH_END 255   // logistic weight of an end mark (above every limit)

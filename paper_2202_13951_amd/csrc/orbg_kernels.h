@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #define ORBG_MAX_CODES 8       // codes one launch may mix
+#define ORBG_MATCH_M 10        // check bits from which a search rarely ends in its first steps
 #define ORBG_MIXED_COLS 2048   // packed columns of all codes of a mixed launch (sum of n)
 
 namespace orbg {
@@ -88,13 +89,21 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 #define ORBG_OPEN 2
 
 // The match search decodes every code that has its tables, but not the 1-line
-// order, nor where the first batch alone or the naive launch is asked for.
+// order, nor where the first batch alone or the naive launch is asked for; with
+// a batch order it takes codes of ORBG_MATCH_M check bits or more (with fewer,
+// 4096 patterns hold many members, and the first steps of the order find one).
+inline bool many_checks(const DecodeArgs& a)
+{
+    for (int i = 0; i < a.codes.ncodes; ++i)
+        if (a.codes.c[i].m < ORBG_MATCH_M) return false;
+    return true;
+}
 inline bool uses_match(const DecodeArgs& a)
 {
     if (a.oneline || a.list_only || a.p.naive) return false;
     for (int i = 0; i < a.codes.ncodes; ++i)
         if (a.codes.c[i].sets == nullptr) return false;
-    return true;
+    return a.order == nullptr || many_checks(a);
 }
 
 }  // namespace orbg

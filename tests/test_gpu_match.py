@@ -25,6 +25,7 @@ def _check(got, want, tag):
 
 
 @pytest.mark.parametrize("n,m,blocks,ebn0,budget", [
+    (9, 1, 50, 2.0, 512), (13, 3, 70, 1.0, 8192), (60, 6, 33000, 3.0, 5000), (120, 8, 70000, 4.0, 3000),
     (11, 10, 400, 2.0, 2048), (12, 10, DIRECT + 9, 3.0, 4096), (40, 10, DIRECT + 1, 4.0, 3000),
     (64, 33, DIRECT + 63, 4.0, 300), (65, 11, DIRECT, 4.0, 2000), (128, 64, DIRECT + 7, 4.0, 100),
     (129, 24, DIRECT + 5, 4.5, 700), (257, 20, DIRECT + 1, 5.5, 1000), (513, 22, DIRECT + 3, 6.0, 300),
