@@ -312,47 +312,17 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
             wave_lds_sync();
             reach = reach == (uint32_t)n ? ALL : reach;
         }
-        // the whole block's ranks, when the search goes past the first ones
-        auto rank_all = [&]() {
-            uint32_t all[NK];
-            rank_order<NK>(x, n, c.rdepth, 0, all);
-#pragma unroll
-            for (int j = 0; j < NK; ++j) {
-                const int e = lane * NK + j;
-                if (e < c.rdepth && e + 1 < ORBG_MATCH_RANKS) L.pi[e + 1] = (uint16_t)all[j];
-            }
-            wave_lds_sync();
-            S g[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int r = lane + 1 + j * ORBG_WAVE;
-                const bool in = r <= c.rdepth && r < ORBG_MATCH_RANKS;
-                const S col = cols[in ? L.pi[r] : 0];
-                g[j] = in ? col : (S)0;
-            }
-            sv = s0;
-            piv = match_reduce<2, S>(g, sv, L.null, nulls);
-            L.h[lane + 1] = g[0];
-            if (lane + 1 + ORBG_WAVE < ORBG_MATCH_RANKS) L.h[lane + 1 + ORBG_WAVE] = g[1];
-            wave_lds_sync();
-            reach = ALL;
-        };
-        if (reach == 0) rank_all();
-        // scan(limit, visit): all sets of weight <= limit()
-        auto scan = [&](auto&& limit, auto&& visit) {
-            uint32_t t = 0;
-            for (;;) {
-                t = match_scan<S>(c.sets, L, sv, piv, nulls, t, reach, limit, visit);
-                if (reach >= limit()) break;
-                rank_all();
-            }
-        };
-        if constexpr (ORDERED) {
-            // The reordered batches: of the matches among the first 4096
-            // patterns, the one whose batch comes first in the block's order
-            // (a batch that the order leaves out is not tested).
-            uint32_t at = ~0u;
-            auto visit = [&](const Pattern& p) {
+        // Phase 0, with a batch order: of the matches among the first 4096
+        // patterns, the one whose batch comes first in the block's order (a batch
+        // that the order leaves out is not tested).  Phase 1: the earliest match
+        // (in an ordered decode, past those 4096).
+        uint32_t at = ~0u;
+        int phase = ORDERED ? 0 : 1;
+        const Pattern none = {(wlim << 16) | 0xffffu, ~0u, ~0u};   // after every pattern within the limit
+        if (!ORDERED) best = none;
+        auto limit = [&]() { return phase == 0 ? (uint32_t)c.wprefix : pattern_weight(best); };
+        auto visit = [&](const Pattern& p) {
+            if (phase == 0) {
                 const uint32_t i = p.key >> 8 == 0u ? 0u : match_query(p, c.below, c.above) - 1u;
                 if (i >= PREFIX) return;
                 const uint64_t pos = ballot(ordv == i / ORBG_WAVE);
@@ -362,22 +332,57 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
                     at = k;
                     best = p;
                 }
-            };
-            scan([&]() { return (uint32_t)c.wprefix; }, visit);
-            q = at + 1u;                                  // 0: no match
-        }
-        if (!ORDERED || (q == 0 && lim > PREFIX)) {
-            best = {(wlim << 16) | 0xffffu, ~0u, ~0u};    // after every pattern within the limit
-            auto visit = [&](const Pattern& p) {
-                if (p.key < best.key || (p.key == best.key && (p.x < best.x || (p.x == best.x && p.y < best.y)))) {
-                    if (ORDERED && (p.key >> 8 == 0u || (pattern_weight(p) <= (uint32_t)c.wprefix &&
-                                                         match_query(p, c.below, c.above) <= PREFIX)))
-                        return;                           // in the reordered prefix
-                    best = p;
+            } else if (p.key < best.key || (p.key == best.key && (p.x < best.x || (p.x == best.x && p.y < best.y)))) {
+                if (ORDERED && (p.key >> 8 == 0u || (pattern_weight(p) <= (uint32_t)c.wprefix &&
+                                                     match_query(p, c.below, c.above) <= PREFIX)))
+                    return;                               // in the reordered prefix
+                best = p;
+            }
+        };
+        // (one copy of the whole ranking and of the scan in the kernel: with two of
+        // each, and two of the whole block for alternating row buffers, the code
+        // came to 60 KB and the waves waited for instructions)
+        uint32_t t = 0;
+        for (;;) {
+            if (reach == 0) {                             // the whole block's ranks
+                uint32_t all[NK];
+                rank_order<NK>(x, n, c.rdepth, 0, all);
+#pragma unroll
+                for (int j = 0; j < NK; ++j) {
+                    const int e = lane * NK + j;
+                    if (e < c.rdepth && e + 1 < ORBG_MATCH_RANKS) L.pi[e + 1] = (uint16_t)all[j];
                 }
-            };
-            scan([&]() { return pattern_weight(best); }, visit);
+                wave_lds_sync();
+                S g[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int r = lane + 1 + j * ORBG_WAVE;
+                    const bool in = r <= c.rdepth && r < ORBG_MATCH_RANKS;
+                    const S col = cols[in ? L.pi[r] : 0];
+                    g[j] = in ? col : (S)0;
+                }
+                sv = s0;
+                piv = match_reduce<2, S>(g, sv, L.null, nulls);
+                L.h[lane + 1] = g[0];
+                if (lane + 1 + ORBG_WAVE < ORBG_MATCH_RANKS) L.h[lane + 1 + ORBG_WAVE] = g[1];
+                wave_lds_sync();
+                reach = ALL;
+            }
+            t = match_scan<S>(c.sets, L, sv, piv, nulls, t, reach, limit, visit);
+            if (reach < limit()) {                        // more ranks are needed
+                reach = 0;
+                continue;
+            }
+            if (ORDERED && phase == 0) {
+                q = at + 1u;                              // 0: no match
+                if (q != 0 || lim <= PREFIX) break;
+                phase = 1;
+                best = none;
+                t = 0;
+                continue;
+            }
             if (best.x != ~0u) q = match_query(best, c.below, c.above);
+            break;
         }
         if (q > lim) q = 0;
     }
@@ -482,8 +487,8 @@ match_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
         load_row_buf<NK>(make_buf(llr + (rv ? row : 0), rv ? (uint32_t)codes.c[ci].n * 4u : 0u), f.x);
         f.ordv = ORDERED ? load_order_buf(make_buf(order + (ok ? i : 0) * 64, ok ? 64u : 0u)) : 0u;
     };
-    In fa, fb;
-    fetch(fa, b);
+    In cur_in, next_in;
+    fetch(cur_in, b);
     for (int ci = 0; ci < (MIXED ? codes.ncodes : 1); ++ci) {
         const CodeDesc& c = codes.c[ci];
         for (int i = threadIdx.x; i < c.n; i += ORBG_WAVE) s_cols[c.col_base + i] = (S)c.cols[i];
@@ -491,24 +496,18 @@ match_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     }
     wave_lds_sync();
     uint32_t guess = 0x40800000u;                         // |LLR| = 4
-    auto decode = [&](const In& f) {
-        const CodeDesc& c = codes.c[MIXED ? f.ci : 0];
-        uint64_t hr[NK];
-        load_hrows_pad<NK>(s_rows + c.row_base, c.m, c.nk, hr);
-        match_block<NK, ORDERED, S>(f.x, hr, c, s_cols + c.col_base, L, budget, f.ordv,
-                                    make_buf(cw + (f.row >= 0 ? f.row : 0), f.row >= 0 ? (uint32_t)c.n : 0u),
-                                    queries + f.oid, abandoned + f.oid, guess, NoOffs{});
-    };
-    // the next block's row loads while this one is decoded; the two buffers alternate
+    // the next block's row loads while this one is decoded
     for (;;) {
         b = cur.next();
-        fetch(fb, b);
-        decode(fa);
+        fetch(next_in, b);
+        const CodeDesc& c = codes.c[MIXED ? cur_in.ci : 0];
+        uint64_t hr[NK];
+        load_hrows_pad<NK>(s_rows + c.row_base, c.m, c.nk, hr);
+        match_block<NK, ORDERED, S>(cur_in.x, hr, c, s_cols + c.col_base, L, budget, cur_in.ordv,
+                                    make_buf(cw + (cur_in.row >= 0 ? cur_in.row : 0), cur_in.row >= 0 ? (uint32_t)c.n : 0u),
+                                    queries + cur_in.oid, abandoned + cur_in.oid, guess, NoOffs{});
         if (b < 0) break;
-        b = cur.next();
-        fetch(fa, b);
-        decode(fb);
-        if (b < 0) break;
+        cur_in = next_in;
     }
 }
 

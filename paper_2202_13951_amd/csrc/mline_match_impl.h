@@ -761,19 +761,15 @@ __global__ void __launch_bounds__(ORBG_WAVE) mline_match_kernel(MlineArgs a)
     auto fetch = [&](float (&x)[NK], int64_t b) {
         load_row_buf<NK>(make_buf(a.llr + (b < a.nblocks ? b * (int64_t)n : 0), b < a.nblocks ? (uint32_t)n * 4u : 0u), x);
     };
-    auto decode = [&](const float (&x)[NK], int64_t b) { mline_match_block<NK, S, false>(a, a.sets, L, x, hrow, b); };
-    float xa[NK], xb[NK];
+    float x[NK], next[NK];
     int64_t b = blockIdx.x;
-    fetch(xa, b);
-    for (;;) {
-        if (b >= a.nblocks) break;
-        fetch(xb, b + gridDim.x);
-        decode(xa, b);
+    fetch(x, b);
+    while (b < a.nblocks) {
+        fetch(next, b + gridDim.x);                       // loads while this block is decoded
+        mline_match_block<NK, S, false>(a, a.sets, L, x, hrow, b);
         b += gridDim.x;
-        if (b >= a.nblocks) break;
-        fetch(xa, b + gridDim.x);
-        decode(xb, b);
-        b += gridDim.x;
+#pragma unroll
+        for (int j = 0; j < NK; ++j) x[j] = next[j];
     }
 }
 
