@@ -119,9 +119,26 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream)
     // a batch order, or a small batch whose searches are long enough: one launch
     if (a.order || (a.nblocks <= ORBG_MATCH_DIRECT && many_checks(a))) return launch_match(a, nk, s32, false, stream);
     // else a first pass (screening and the first batch of patterns), then the
-    // match search of the blocks it leaves
-    const hipError_t e = launch_first(a, nk, s32, stream);
-    return e != hipSuccess ? e : launch_match(a, nk, s32, true, stream);
+    // match search of the blocks it leaves; at most ORBG_PAST bytes of codewords
+    // at a time (the first pass addresses them by 32-bit offsets)
+    const int64_t most = a.mixed ? 0x40000000ll : 0x40000000ll / a.codes.c[0].n;
+    for (int64_t from = 0; from < a.nblocks; from += most) {
+        DecodeArgs p = a;
+        p.nblocks = a.nblocks - from < most ? a.nblocks - from : most;
+        if (a.mixed) {
+            p.block_code += from;
+            p.row_off += from;
+        } else {
+            p.llr += from * a.codes.c[0].n;
+            p.cw += from * a.codes.c[0].n;
+        }
+        p.queries += from;
+        p.abandoned += from;
+        hipError_t e = launch_first(p, nk, s32, stream);
+        if (e == hipSuccess) e = launch_match(p, nk, s32, true, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace orbg

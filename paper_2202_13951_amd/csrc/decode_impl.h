@@ -208,14 +208,13 @@ template <int NK, typename S>
 __device__ __forceinline__ S hard_decision(const float (&x)[NK], int n, const uint64_t (&hrow)[NK],
                                            bool (&ybit)[NK])
 {
-    const int lane = lane_id();
     // the parity of a sum of popcounts is the parity of the XOR of the words:
     // the masked words are folded first (a AND b XOR c in one three-input bit
     // operation, truth table 0x6a), one popcount at the end
     uint32_t acc = 0;
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
-        ybit[j] = (j * ORBG_WAVE + lane < n) && (x[j] > 0.0f);
+        ybit[j] = x[j] > 0.0f;                            // (lanes past the row hold zeros)
         const uint64_t y = ballot(ybit[j]);
         acc = __builtin_amdgcn_bitop3_b32((uint32_t)hrow[j], (uint32_t)y, acc, 0x6a);
         acc = __builtin_amdgcn_bitop3_b32((uint32_t)(hrow[j] >> 32), (uint32_t)(y >> 32), acc, 0x6a);

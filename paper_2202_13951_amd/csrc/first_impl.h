@@ -24,9 +24,18 @@ namespace orbg {
 #define ORBG_FIRST_SLOTS 32      // staged blocks: at most 3 left over and 16 of one group (a power of two)
 #define ORBG_FIRST_ROW 20        // ranks 0..16 of a sorted block, padded
 
+// Words of a staged block: its hard decision (2 NK), syndrome (2), index and
+// (ranks | code << 8); one per lane of the store, so a power of two.
+template <int NK>
+struct FirstWords {
+    static constexpr int SYN = 2 * NK, ID = 2 * NK + 2, INFO = 2 * NK + 3;
+    static constexpr int W = NK <= 2 ? 8 : NK == 4 ? 16 : NK == 8 ? 32 : 64;
+};
+
 template <int NK, typename S>
 struct FirstLds {
     uint32_t key[ORBG_FIRST_SLOTS * 16];
+    uint32_t word[ORBG_FIRST_SLOTS * FirstWords<NK>::W + ORBG_WAVE];   // (the last 64: lanes past W)
     S h[4 * ORBG_FIRST_ROW];             // columns by rank of four sorted blocks (rank 0: zero)
     uint32_t pi[4 * ORBG_FIRST_ROW];     // their received indices (rank 0: none)
 };
@@ -84,10 +93,16 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     if (HOIST) load_hrows<NK>(s_rows, codes.c[0].m, hrow0);
     LaneOffs<NK> lo = lane_offsets<NK>(MIXED ? NK * ORBG_WAVE : codes.c[0].n);
 
-    // staged blocks: slot k's values in lane k
-    uint32_t ylo[NK], yhi[NK], syn_lo = 0, syn_hi = 0, id_lo = 0, id_hi = 0, meta = 0;   // meta: ranks | code << 8
-#pragma unroll
-    for (int j = 0; j < NK; ++j) ylo[j] = yhi[j] = 0;
+    using Q = FirstWords<NK>;
+    // this lane's word of slot 0; lanes past W write beside the slots
+    uint32_t* const my_word = &L.word[lane < Q::W ? lane : ORBG_FIRST_SLOTS * Q::W + lane];
+    const uint32_t word_step = lane < Q::W ? Q::W : 0u;
+    // one code: codewords, query counts and flags of all blocks (the host keeps
+    // the batch's codewords within ORBG_PAST bytes); a block is a scalar offset
+    const uint32_t n0 = (uint32_t)codes.c[0].n;
+    const buf_t cw_all = make_buf(cw, MIXED ? 0u : (uint32_t)nblocks * n0);
+    const buf_t q_all = make_buf(queries, MIXED ? 0u : (uint32_t)nblocks * 8u);
+    const buf_t ab_all = make_buf(abandoned, MIXED ? 0u : (uint32_t)nblocks);
     uint32_t head = 0, staged = 0;
     float tau = 2.0f;                                     // threshold, carried from block to block
 
@@ -100,23 +115,40 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
         return uniform_i64((row >= 0 && row <= row_limit - codes.c[ci].n) ? row : -1);
     };
     // codeword y, query count and flag of block b
-    auto write = [&](int64_t b, int ci, int64_t row, const uint64_t (&y)[NK], uint32_t q) {
-        const int n = codes.c[ci].n;
-        const buf_t cb = make_buf(cw + (row >= 0 ? row : 0), row >= 0 ? (uint32_t)n : 0u);
+    auto write = [&](uint32_t b, int ci, int64_t row, const uint64_t (&y)[NK], uint32_t q) {
+        const u32x2_t qv = {q, 0u};
+        if constexpr (!MIXED) {
 #pragma unroll
-        for (int j = 0; j < NK; ++j)
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(__builtin_amdgcn_inverse_ballot_w64(y[j]) ? 1 : 0), cb, lo.c[j],
-                                                 0, 0);
-        write_result(queries + b, abandoned + b, q, false, lo.r);
+            for (int j = 0; j < NK; ++j)
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(__builtin_amdgcn_inverse_ballot_w64(y[j]) ? 1 : 0), cw_all,
+                                                     lo.c[j], b * n0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(qv, q_all, lo.r, b * 8u, 0);
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)0, ab_all, lo.r, b, 0);
+        } else {
+            const buf_t cb = make_buf(cw + (row >= 0 ? row : 0), row >= 0 ? (uint32_t)codes.c[ci].n : 0u);
+#pragma unroll
+            for (int j = 0; j < NK; ++j)
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(__builtin_amdgcn_inverse_ballot_w64(y[j]) ? 1 : 0), cb,
+                                                     lo.c[j], 0, 0);
+            write_result(queries + b, abandoned + b, q, false, lo.r);
+        }
+    };
+    auto mark = [&](uint32_t b) {
+        if constexpr (!MIXED) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)ORBG_OPEN, ab_all, lo.r, b, 0);
+        else __builtin_amdgcn_raw_buffer_store_b8((uint8_t)ORBG_OPEN, make_buf(abandoned + b, 1), lo.r, 0, 0);
     };
 
     // Sorts the `cnt` (1..4) oldest staged blocks and tests their patterns.
     auto flush = [&](uint32_t cnt) {
         const uint32_t sub = (uint32_t)lane >> 4, in = (uint32_t)lane & 15u;
         const uint32_t slot = (head + sub) & (ORBG_FIRST_SLOTS - 1);
-        const uint32_t mt = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(slot * 4u), (int)meta);
-        const uint32_t known = sub < cnt ? mt & 0xffu : 0u;
         wave_lds_sync();
+        const uint32_t mt = L.word[slot * Q::W + Q::INFO];
+        uint32_t words[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            words[j] = L.word[((head + (uint32_t)j) & (ORBG_FIRST_SLOTS - 1)) * Q::W + ((uint32_t)lane & (Q::W - 1))];
+        const uint32_t known = sub < cnt ? mt & 0xffu : 0u;
         uint32_t k1[1] = {in < known ? L.key[slot * 16u + in] : 0xffffffffu};
         bitonic_stage32<1, 2, 8>(k1);
         // the last stage ascending in every row
@@ -145,13 +177,10 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if ((uint32_t)j >= cnt) break;
-            const int sl = (int)((head + j) & (ORBG_FIRST_SLOTS - 1));
-            const uint32_t info = (uint32_t)__builtin_amdgcn_readlane((int)meta, sl);
-            const S s0 = sizeof(S) == 4 ? (S)(uint32_t)__builtin_amdgcn_readlane((int)syn_lo, sl)
-                                        : (S)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)syn_hi, sl) << 32) |
-                                              (uint32_t)__builtin_amdgcn_readlane((int)syn_lo, sl));
-            const int64_t b = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)id_hi, sl) << 32) |
-                                        (uint32_t)__builtin_amdgcn_readlane((int)id_lo, sl));
+            auto get = [&](int k) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)words[j], k); };
+            const uint32_t info = get(Q::INFO);
+            const S s0 = sizeof(S) == 4 ? (S)get(Q::SYN) : (S)(((uint64_t)get(Q::SYN + 1) << 32) | get(Q::SYN));
+            const uint32_t b = get(Q::ID);
             const S* h = L.h + j * ORBG_FIRST_ROW;
             const S v = xor3<S>(xor3<S>(s0, h[a[0]], h[a[1]]), h[a[2]], h[a[3]]);
             const uint64_t hits = ballot(v == 0 && wpat <= (info & 0xffu));
@@ -159,21 +188,21 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
             if (hits != 0 && ((ties >> (16 * j)) & 0xffffull) == 0ull && wl < budget) {
                 uint64_t y[NK];
 #pragma unroll
-                for (int k = 0; k < NK; ++k)
-                    y[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)yhi[k], sl) << 32) |
-                           (uint32_t)__builtin_amdgcn_readlane((int)ylo[k], sl);
+                for (int k = 0; k < NK; ++k) y[k] = ((uint64_t)get(2 * k + 1) << 32) | get(2 * k);
+                // flips as lane masks (compares are vector work: the scalar unit is
+                // the busier one)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const uint32_t p =
                         (uint32_t)__builtin_amdgcn_readlane((int)L.pi[j * ORBG_FIRST_ROW + a[u]], (int)wl);
 #pragma unroll
-                    for (int k = 0; k < NK; ++k) y[k] ^= (p >> 6) == (uint32_t)k ? 1ull << (p & 63u) : 0ull;
+                    for (int k = 0; k < NK; ++k) y[k] ^= ballot((uint32_t)(k * ORBG_WAVE + lane) == p);
                 }
                 int ci = 0;
-                const int64_t row = row_of(b, ci);
+                const int64_t row = MIXED ? row_of(b, ci) : 0;
                 write(b, ci, row, y, wl + 1u);
             } else {
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)ORBG_OPEN, make_buf(abandoned + b, 1), lo.r, 0, 0);
+                mark(b);
             }
         }
         wave_lds_sync();
@@ -224,7 +253,7 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
 #pragma unroll
             for (int j = 0; j < NK; ++j) y[j] = ballot(yb[j]);
             if (s0 == 0) {
-                write(g2 + kk, ci, MIXED ? rows[kk] : (g2 + kk) * c.n, y, 1u);
+                write((uint32_t)g2 + kk, ci, MIXED ? rows[kk] : 0, y, 1u);
                 continue;
             }
             // threshold: 9 to 16 magnitudes below it, by steps of a quarter and
@@ -243,6 +272,7 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
                 }
             };
             float lo_t = 0.0f, hi_t = 0.0f;               // bracket (0: open)
+#pragma unroll 1
             for (int it = 0; it < 8; ++it) {
                 pick();
                 if (below >= ORBG_FIRST_MIN && below <= 16u) break;
@@ -254,7 +284,7 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
                 tau = __uint_as_float(uniform_u32(__float_as_uint(lo_t == 0.0f || hi_t == 0.0f ? open : mid)));
             }
             if (below < ORBG_FIRST_MIN || below > 16u || c.n < ORBG_FIRST_N) {
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)ORBG_OPEN, make_buf(abandoned + g2 + kk, 1), lo.r, 0, 0);
+                mark((uint32_t)g2 + kk);
                 continue;
             }
             const uint32_t slot = (head + staged) & (ORBG_FIRST_SLOTS - 1);
@@ -269,16 +299,17 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
                 if (__builtin_amdgcn_inverse_ballot_w64(mk[j])) L.key[to] = key;
                 at += (uint32_t)__builtin_popcountll(mk[j]);
             }
+            uint32_t wv = 0;
 #pragma unroll
             for (int j = 0; j < NK; ++j) {
-                writelane(ylo[j], (uint32_t)y[j], slot);
-                writelane(yhi[j], (uint32_t)(y[j] >> 32), slot);
+                writelane(wv, (uint32_t)y[j], 2 * j);
+                writelane(wv, (uint32_t)(y[j] >> 32), 2 * j + 1);
             }
-            writelane(syn_lo, (uint32_t)s0, slot);
-            if (sizeof(S) == 8) writelane(syn_hi, (uint32_t)((uint64_t)s0 >> 32), slot);
-            writelane(id_lo, (uint32_t)(uint64_t)(g2 + kk), slot);
-            writelane(id_hi, (uint32_t)((uint64_t)(g2 + kk) >> 32), slot);
-            writelane(meta, below | ((uint32_t)ci << 8), slot);
+            writelane(wv, (uint32_t)s0, Q::SYN);
+            if (sizeof(S) == 8) writelane(wv, (uint32_t)((uint64_t)s0 >> 32), Q::SYN + 1);
+            writelane(wv, (uint32_t)g2 + kk, Q::ID);
+            writelane(wv, below | ((uint32_t)ci << 8), Q::INFO);
+            my_word[slot * word_step] = wv;
             ++staged;
         }
         while (staged >= 4u) flush(4u);

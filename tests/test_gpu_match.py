@@ -157,3 +157,19 @@ def test_mline_curves(gpu_device, n, m, segments, curve):
     want = O.decode_mline(H, llr, budget, segments, threads=THREADS)
     _check(got[:3], want[:3], f"mline {curve} n={n}")
     assert (got[3].cpu().numpy() == want[3]).all()
+
+
+def test_more_codewords_than_one_launch_addresses(gpu_device):
+    """The first pass addresses codewords by 32-bit offsets, 2^30 bytes to a
+    launch: a larger batch equals the same blocks decoded in two parts."""
+    n, blocks, budget = 1024, (1 << 20) + 70, 200
+    print(f"match slabs blocks={blocks}", flush=True)
+    H = codes.rlc_H(n, n - 12, seed=5)
+    g = torch.Generator(device=gpu_device).manual_seed(3)
+    llr = torch.empty(blocks, n, device=gpu_device)
+    for part in llr.split(1 << 17):
+        part.normal_(-4.0, 2.0, generator=g)
+    whole = binding.orbg_decode(H, llr, budget)
+    half = blocks // 2 + 1
+    for got, a, b in zip(whole, binding.orbg_decode(H, llr[:half], budget), binding.orbg_decode(H, llr[half:], budget)):
+        assert torch.equal(got[:half], a) and torch.equal(got[half:], b)
