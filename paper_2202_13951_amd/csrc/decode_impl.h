@@ -245,7 +245,7 @@ __device__ __forceinline__ void rank_order(const float (&x)[NK], int n, int rdep
         const uint32_t mag = (i < n) ? (__float_as_uint(x[j]) & 0x7fffffffu) : 0x7fffffffu;
         key[j] = ((mag >> (IB - 1)) << IB) | (uint32_t)i;
     }
-    bitonic_sort32<NK>(key);
+    sort32<NK>(key);
     const uint32_t next0 = (uint32_t)__shfl_down((int)key[0], 1, ORBG_WAVE);
     bool tie = false;
 #pragma unroll
@@ -388,7 +388,7 @@ __device__ __forceinline__ bool rank_first(const float (&x)[NK], int n, int ra, 
     wave_lds_sync();
     uint32_t k1[1] = {(uint32_t)lane < cnt ? stage[lane] : 0xffffffffu};
     wave_lds_sync();
-    bitonic_sort32_groups<32>(k1);
+    sort32<1, 32>(k1);
     const uint32_t next = (uint32_t)__shfl_down((int)k1[0], 1, ORBG_WAVE);
     const bool tie = lane < ra && (uint32_t)lane + 1 < cnt && ((k1[0] ^ next) >> IB) == 0u;
     if (ballot(tie) != 0ull) return false;

@@ -150,19 +150,7 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
             words[j] = L.word[((head + (uint32_t)j) & (ORBG_FIRST_SLOTS - 1)) * Q::W + ((uint32_t)lane & (Q::W - 1))];
         const uint32_t known = sub < cnt ? mt & 0xffu : 0u;
         uint32_t k1[1] = {in < known ? L.key[slot * 16u + in] : 0xffffffffu};
-        bitonic_stage32<1, 2, 8>(k1);
-        // the last stage ascending in every row
-        {
-            uint32_t p;
-            p = lane_xor<8>(k1[0]);
-            k1[0] = ((p < k1[0]) == lane_bit<0x00ff00ff00ff00ffull>()) ? p : k1[0];
-            p = lane_xor<4>(k1[0]);
-            k1[0] = ((p < k1[0]) == lane_bit<0x0f0f0f0f0f0f0f0full>()) ? p : k1[0];
-            p = lane_xor<2>(k1[0]);
-            k1[0] = ((p < k1[0]) == lane_bit<0x3333333333333333ull>()) ? p : k1[0];
-            p = lane_xor<1>(k1[0]);
-            k1[0] = ((p < k1[0]) == lane_bit<0x5555555555555555ull>()) ? p : k1[0];
-        }
+        sort32<1, 16>(k1);
         const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)k1[0], 0x101, 0xF, 0xF, false);   // row_shl:1
         const uint64_t ties = ballot(in + 1u < known && ((k1[0] ^ next) >> IB) == 0u);
         const uint32_t idx = k1[0] & ((1u << IB) - 1u);

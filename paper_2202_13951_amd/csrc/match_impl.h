@@ -119,83 +119,81 @@ __device__ __forceinline__ uint32_t match_query(const Pattern& p, const uint32_t
     return 1u + wave_sum(v);
 }
 
-// The least reliable ranks of a block: a threshold on the truncated magnitude
-// with want <= #(keys below it) <= 64, moved from the caller's guess as in
-// rank_first; the keys below it are gathered through LDS and sorted one per
-// lane.  Lane l < cnt then holds the received index of rank l + 1.  Returns
-// cnt, or 0 when no threshold is found or two of the keys share a truncated
-// magnitude (their order would need the full keys).
+// The least reliable ranks of a block: a threshold on |LLR| with want <=
+// #(magnitudes below it) <= 63, moved from the caller's guess by steps of a
+// quarter and then by halves; the keys below it are gathered through LDS and
+// sorted one per lane.  Lane l < cnt then holds the received index of rank
+// l + 1.  Returns cnt, or 0 when no threshold is found or two of the keys share
+// a truncated magnitude (their order would need the full keys).
 template <int NK>
-__device__ __forceinline__ uint32_t rank_some(const float (&x)[NK], int n, uint32_t want, uint32_t& guess,
+__device__ __forceinline__ uint32_t rank_some(const float (&x)[NK], int n, uint32_t want, float& guess,
                                               uint32_t* stage, uint32_t& idx)
 {
     constexpr int IB = IndexBits<NK>::value;
-    constexpr uint32_t PMAX = 1u << (32 - IB);          // truncated magnitudes are < PMAX
-    constexpr uint32_t OCT = 1u << (24 - IB);           // one binade in truncated-magnitude units
+    constexpr uint32_t MOST = ORBG_WAVE - 1;
     const int lane = lane_id();
-    uint32_t key[NK];
-#pragma unroll
-    for (int j = 0; j < NK; ++j) {
-        const int i = j * ORBG_WAVE + lane;
-        // lanes past n: the largest truncated magnitude, which no threshold passes
-        const uint32_t mag = i < n ? (__float_as_uint(x[j]) & 0x7fffffffu) : 0x7fffffffu;
-        key[j] = ((mag >> (IB - 1)) << IB) | (uint32_t)i;
-    }
-    uint32_t t = guess >> (IB - 1), lo = 0, hi = PMAX - 1, cnt = 0;
+    float tau = guess, lo_t = 0.0f, hi_t = 0.0f;          // bracket (0: open)
+    uint64_t mk[NK];
+    uint32_t cnt = 0;
     bool ok = false;
+#pragma unroll 1
     for (int it = 0; it < 10; ++it) {
         cnt = 0;
 #pragma unroll
-        for (int j = 0; j < NK; ++j) cnt += (uint32_t)__builtin_popcountll(ballot((key[j] >> IB) < t));
-        if (cnt >= want && cnt <= (uint32_t)ORBG_WAVE) { ok = true; break; }
-        if (cnt < want) {
-            lo = t;
-            t = (hi == PMAX - 1) ? (t < PMAX - 1 - OCT ? t + OCT / 2 : PMAX - 1) : lo + (hi - lo) / 2;
-        } else {
-            hi = t;
-            t = (lo == 0) ? (t > OCT ? t - OCT / 2 : t / 2) : lo + (hi - lo) / 2;
+        for (int j = 0; j < NK; ++j) {
+            // lanes past n hold zeros and are no candidates
+            mk[j] = ballot(fabsf(x[j]) < tau) & (n >= (j + 1) * ORBG_WAVE ? ~0ull
+                                                 : n <= j * ORBG_WAVE    ? 0ull
+                                                                         : (1ull << (n & 63)) - 1ull);
+            cnt += (uint32_t)__builtin_popcountll(mk[j]);
         }
-        t = uniform_u32(t);
+        if (cnt >= want && cnt <= MOST) { ok = true; break; }
+        const bool up = cnt < want;
+        lo_t = up ? tau : lo_t;
+        hi_t = up ? hi_t : tau;
+        const float open = tau * (up ? 1.25f : 0.8f);
+        const float mid = 0.5f * (lo_t + hi_t);
+        tau = __uint_as_float(uniform_u32(__float_as_uint(lo_t == 0.0f || hi_t == 0.0f ? open : mid)));
     }
     if (!ok) {
-        guess = uniform_u32(t << (IB - 1));              // the next block goes on from here
+        guess = tau > 0.0f && tau < INFINITY ? tau : 1.0f;   // the next block goes on from here
         return 0;
     }
-    uint32_t base = 0;
+    uint32_t at = 0;
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
-        const bool c = (key[j] >> IB) < t;
-        const uint64_t m = ballot(c);
-        const uint32_t slot =
-            base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if (c) stage[slot] = key[j];
-        base += (uint32_t)__builtin_popcountll(m);
+        const uint32_t key = ((__float_as_uint(x[j]) & 0x7fffffffu) >> (IB - 1)) << IB | (uint32_t)(j * ORBG_WAVE + lane);
+        const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(mk[j] >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mk[j], at));
+        if (__builtin_amdgcn_inverse_ballot_w64(mk[j])) stage[to] = key;
+        at += (uint32_t)__builtin_popcountll(mk[j]);
     }
     wave_lds_sync();
     uint32_t k1[1] = {(uint32_t)lane < cnt ? stage[lane] : 0xffffffffu};
     wave_lds_sync();
-    bitonic_sort32<1>(k1);
+    sort32<1>(k1);
     const uint32_t next = (uint32_t)__shfl_down((int)k1[0], 1, ORBG_WAVE);
     const bool tie = (uint32_t)lane + 1 < cnt && ((k1[0] ^ next) >> IB) == 0u;
     if (ballot(tie) != 0ull) return 0;
     idx = k1[0] & ((1u << IB) - 1u);
     // next block's guess: the middle of the window
-    const uint32_t mid = (want + (uint32_t)ORBG_WAVE) / 2;
+    const uint32_t mid = (want + MOST) / 2;
     const uint32_t e = (mid < cnt ? mid : cnt) - 1;
     const uint32_t g = ((uint32_t)__builtin_amdgcn_readlane((int)k1[0], (int)e) >> IB) + 1u;
-    guess = uniform_u32(g << (IB - 1));
+    guess = __uint_as_float(g << (IB - 1));
     return cnt;
 }
 
 // Gauss-Jordan steps on the columns of ranks 1..8 (rank r in lane r - 1 of
-// g[0]), applied to g and to s0; returns the mask of independent ranks (bit
+// g[0]), applied to g and to s0 (in a lane of g that holds no rank, or in *sv);
+// returns the mask of independent ranks (bit
 // r - 1), the combinations of the dependent ones in null[0 .. nulls - 1].
 // Column k + 1 with a bit outside the pivots so far: bit k of every vector
 // takes one of those bits too if the column's bit k is clear (a row operation;
 // bits at or above n - k start as zero rows), and the column's other bits are
 // cleared wherever bit k is set.
 template <int NC, typename S>
-__device__ __forceinline__ S match_reduce(S (&g)[NC], S& sv, uint32_t* null, uint32_t& nulls)
+__device__ __forceinline__ S match_reduce(S (&g)[NC], uint32_t* null, uint32_t& nulls, S* sv = nullptr)
 {
     S piv = 0;
     nulls = 0;
@@ -212,11 +210,11 @@ __device__ __forceinline__ S match_reduce(S (&g)[NC], S& sv, uint32_t* null, uin
                 const int b = sizeof(S) == 4 ? __builtin_ctz((uint32_t)t) : __builtin_ctzll((uint64_t)t);
 #pragma unroll
                 for (int j = 0; j < NC; ++j) g[j] ^= ((g[j] >> b) & 1) << k;
-                sv ^= ((sv >> b) & 1) << k;
+                if (sv) *sv ^= ((*sv >> b) & 1) << k;
             }
 #pragma unroll
             for (int j = 0; j < NC; ++j) g[j] ^= ((S)0 - ((g[j] >> k) & 1)) & pm;
-            sv ^= ((S)0 - ((sv >> k) & 1)) & pm;
+            if (sv) *sv ^= ((S)0 - ((*sv >> k) & 1)) & pm;
             piv |= (S)1 << k;
         }
     }
@@ -280,7 +278,7 @@ template <int NK, bool ORDERED, typename S, class LO>
 __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t (&hrow)[NK], const CodeDesc& c,
                                             const S* __restrict__ cols, MatchLds<S>& L, uint32_t budget,
                                             uint32_t ordv, buf_t cw_row, uint64_t* q_out, uint8_t* ab_out,
-                                            uint32_t& guess, const LO& lo)
+                                            float& guess, const LO& lo)
 {
     const int lane = lane_id();
     const int n = c.n;
@@ -305,8 +303,9 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
         if (reach != 0) {
             S g[1];
             const S col = cols[(uint32_t)lane < reach ? idx : 0u];
-            g[0] = (uint32_t)lane < reach ? col : (S)0;
-            piv = match_reduce<1, S>(g, sv, L.null, nulls);
+            g[0] = (uint32_t)lane < reach ? col : s0;
+            piv = match_reduce<1, S>(g, L.null, nulls);
+            sv = readlane_s<S>(g[0], ORBG_WAVE - 1);
             L.h[lane + 1] = g[0];
             L.pi[lane + 1] = (uint16_t)idx;
             wave_lds_sync();
@@ -359,10 +358,10 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
                     const int r = lane + 1 + j * ORBG_WAVE;
                     const bool in = r <= c.rdepth && r < ORBG_MATCH_RANKS;
                     const S col = cols[in ? L.pi[r] : 0];
-                    g[j] = in ? col : (S)0;
+                    g[j] = in ? col : j == 1 && lane == ORBG_WAVE - 1 ? s0 : (S)0;
                 }
-                sv = s0;
-                piv = match_reduce<2, S>(g, sv, L.null, nulls);
+                piv = match_reduce<2, S>(g, L.null, nulls);
+                sv = readlane_s<S>(g[1], ORBG_WAVE - 1);
                 L.h[lane + 1] = g[0];
                 if (lane + 1 + ORBG_WAVE < ORBG_MATCH_RANKS) L.h[lane + 1 + ORBG_WAVE] = g[1];
                 wave_lds_sync();
@@ -495,14 +494,22 @@ match_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
         for (int i = threadIdx.x; i < c.m * c.nk; i += ORBG_WAVE) s_rows[c.row_base + i] = c.rows[i];
     }
     wave_lds_sync();
-    uint32_t guess = 0x40800000u;                         // |LLR| = 4
+    constexpr bool HOIST = !MIXED && NK <= 4;
+    uint64_t hrow0[NK];
+    if (HOIST) load_hrows<NK>(s_rows, codes.c[0].m, hrow0);
+    float guess = 4.0f;
     // the next block's row loads while this one is decoded
     for (;;) {
         b = cur.next();
         fetch(next_in, b);
         const CodeDesc& c = codes.c[MIXED ? cur_in.ci : 0];
         uint64_t hr[NK];
-        load_hrows_pad<NK>(s_rows + c.row_base, c.m, c.nk, hr);
+        if (HOIST) {
+#pragma unroll
+            for (int j = 0; j < NK; ++j) hr[j] = hrow0[j];
+        } else {
+            load_hrows_pad<NK>(s_rows + c.row_base, c.m, c.nk, hr);
+        }
         match_block<NK, ORDERED, S>(cur_in.x, hr, c, s_cols + c.col_base, L, budget, cur_in.ordv,
                                     make_buf(cw + (cur_in.row >= 0 ? cur_in.row : 0), cur_in.row >= 0 ? (uint32_t)c.n : 0u),
                                     queries + cur_in.oid, abandoned + cur_in.oid, guess, NoOffs{});

@@ -359,7 +359,7 @@ struct MmSearch {
                 const uint32_t m = k * ORBG_WAVE + lane;
                 key[k] = mask_weight_of(m) << 8 | m;      // at most 8 x 2^18, below 2^21
             }
-            bitonic_sort32<4>(key);
+            sort32<4>(key);
 #pragma unroll
             for (int k = 0; k < 4; ++k) L.hist[lane * 4 + k] = key[k];
             wave_lds_sync();
@@ -667,7 +667,7 @@ __device__ __forceinline__ int mline_match_block(const MlineArgs& a, const Mline
                 F.vr[j] = r <= n ? weigh(r, sp[j]) : CAP;
                 F.g[j] = r <= n ? (S)a.cols[L.pi[r]] : (S)0;
             }
-            F.piv = match_reduce<NK, S>(F.g, F.sv, L.null, F.nulls);
+            F.piv = match_reduce<NK, S>(F.g, L.null, F.nulls, &F.sv);
 #pragma unroll
             for (int j = 0; j < NK; ++j) {
                 const int r = lane + 1 + j * ORBG_WAVE;

@@ -94,12 +94,11 @@ __device__ __forceinline__ void bitonic_sort(KEY (&key)[NK])
 
 // Value of lane (lane XOR LD) for a wave-constant distance LD, all lanes active:
 // quad permutes for 1 and 2, a half-row mirror composed with a quad reversal for
-// 4 (7 - (i ^ 3) = i ^ 4 inside each group of 8), a half-row rotation for 8, an
-// LDS-crossbar swizzle (xor mask 16 inside 32 lanes) for 16 and a bpermute for 32.
+// 4 (7 - (i ^ 3) = i ^ 4 inside each group of 8), a half-row rotation for 8.
 template <int LD>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v)
 {
-    static_assert(LD == 1 || LD == 2 || LD == 4 || LD == 8 || LD == 16 || LD == 32, "lane distance");
+    static_assert(LD == 1 || LD == 2 || LD == 4 || LD == 8, "lane distance");
     if constexpr (LD == 1) {
         return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
     } else if constexpr (LD == 2) {
@@ -107,31 +106,19 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v)
     } else if constexpr (LD == 4) {
         const int m = __builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);     // row_half_mirror
         return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1B, 0xF, 0xF, false);        // quad_perm [3,2,1,0]
-    } else if constexpr (LD == 8) {
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, false);  // row_ror:8
-    } else if constexpr (LD == 16) {
-        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);               // and 0x1f, xor 0x10
     } else {
-        return (uint32_t)__shfl_xor((int)v, 32, 64);
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, false);  // row_ror:8
     }
 }
 
-// Lane masks of the bitonic network (compile-time constants): in a cross-lane
-// substep of stage `size` at lane distance ld, the lanes that keep the smaller
-// key; in an in-lane substep, the lanes whose register j runs descending.
-constexpr uint64_t keep_min_mask(int nk, int size, int ld)
+// Value of lane (lane XOR M), all lanes active.
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor_mask(uint32_t v)
 {
-    uint64_t m = 0;
-    for (int l = 0; l < 64; ++l)
-        if (((l & ld) == 0) == (((l * nk) & size) == 0)) m |= 1ull << l;
-    return m;
-}
-constexpr uint64_t desc_mask(int nk, int size, int j)
-{
-    uint64_t m = 0;
-    for (int l = 0; l < 64; ++l)
-        if (((l * nk + j) & size) != 0) m |= 1ull << l;
-    return m;
+    if constexpr (M == 3) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x1B, 0xF, 0xF, false);     // quad_perm [3,2,1,0]
+    else if constexpr (M == 7) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);   // row_half_mirror
+    else if constexpr (M == 15) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);  // row_mirror
+    else return lane_xor<M>(v);
 }
 
 // Per-lane bit of a constant lane mask.  The two scalar moves are written out
@@ -148,65 +135,111 @@ __device__ __forceinline__ bool lane_bit()
     return __builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo);
 }
 
-// One in-lane compare-exchange of registers J and J | D (for every J without bit D).
-template <int NK, int SIZE, int D, int J>
-__device__ __forceinline__ void bitonic_inlane32(uint32_t (&key)[NK])
+// All ones in the lanes whose bit BIT is set, zero in the others.
+template <int BIT>
+__device__ __forceinline__ uint32_t lane_fill()
 {
-    if constexpr (J < NK) {
-        if constexpr ((J & D) == 0) {
-            const bool desc = lane_bit<desc_mask(NK, SIZE, J)>();
-            const uint32_t a = key[J], b = key[J | D];
-            const bool sw = (a > b) != desc;
-            key[J] = sw ? b : a;
-            key[J | D] = sw ? a : b;
-        }
-        bitonic_inlane32<NK, SIZE, D, J + 1>(key);
-    }
+    return (uint32_t)((int32_t)((uint32_t)lane_id() << (31 - BIT)) >> 31);
 }
 
-// Substeps D, D/2, ..., 1 of stage SIZE.
-template <int NK, int SIZE, int D>
-__device__ __forceinline__ void bitonic_step32(uint32_t (&key)[NK])
+// Median of three: with c = 0 the smaller, with c = ~0 the larger of a and b
+// (one instruction, so a lane's side of an exchange is an operand, not a select).
+__device__ __forceinline__ uint32_t med3(uint32_t a, uint32_t b, uint32_t c)
+{
+    const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
+    const uint32_t m = hi < c ? hi : c;
+    return lo < m ? m : lo;
+}
+
+constexpr int log2_of(int v) { return v <= 1 ? 0 : 1 + log2_of(v / 2); }
+
+// Substeps D, D / 2, ..., 1, the smaller key to the lower index.
+template <int NK, int D>
+__device__ __forceinline__ void sort_halves(uint32_t (&key)[NK])
 {
     if constexpr (D >= NK) {
         constexpr int LD = D / NK;
-        const bool keep_min = lane_bit<keep_min_mask(NK, SIZE, LD)>();
+        const uint32_t up = lane_fill<log2_of(LD)>();
 #pragma unroll
         for (int j = 0; j < NK; ++j) {
-            const uint32_t p = lane_xor<LD>(key[j]);
-            const bool take_p = (p < key[j]) == keep_min;
-            key[j] = take_p ? p : key[j];
+            if constexpr (LD == 16) {
+                const auto r = __builtin_amdgcn_permlane16_swap(key[j], key[j], false, false);
+                key[j] = med3(r[0], r[1], up);
+            } else if constexpr (LD == 32) {
+                const auto r = __builtin_amdgcn_permlane32_swap(key[j], key[j], false, false);
+                key[j] = med3(r[0], r[1], up);
+            } else {
+                key[j] = med3(lane_xor<LD>(key[j]), key[j], up);
+            }
         }
     } else {
-        bitonic_inlane32<NK, SIZE, D, 0>(key);
+#pragma unroll
+        for (int j = 0; j < NK; ++j)
+            if ((j & D) == 0) {
+                const uint32_t a = key[j], b = key[j | D];
+                key[j] = a < b ? a : b;
+                key[j | D] = a < b ? b : a;
+            }
     }
-    if constexpr (D > 1) bitonic_step32<NK, SIZE, D / 2>(key);
+    if constexpr (D > 1) sort_halves<NK, D / 2>(key);
 }
 
-template <int NK, int SIZE, int MAXSIZE>
-__device__ __forceinline__ void bitonic_stage32(uint32_t (&key)[NK])
+// Stages SIZE .. MAX (up to one row of 16 lanes) with mirrored first substeps.
+template <int NK, int SIZE, int MAX>
+__device__ __forceinline__ void sort_stages(uint32_t (&key)[NK])
 {
-    bitonic_step32<NK, SIZE, SIZE / 2>(key);
-    if constexpr (SIZE < MAXSIZE) bitonic_stage32<NK, SIZE * 2, MAXSIZE>(key);
+    if constexpr (SIZE <= NK) {
+#pragma unroll
+        for (int j = 0; j < NK; ++j) {
+            const int o = j ^ (SIZE - 1);
+            if (j < o) {
+                const uint32_t a = key[j], b = key[o];
+                key[j] = a < b ? a : b;
+                key[o] = a < b ? b : a;
+            }
+        }
+    } else {
+        constexpr int M = SIZE / NK - 1;                  // 1, 3, 7 or 15
+        const uint32_t up = lane_fill<log2_of(M + 1) - 1>();
+        uint32_t p[NK];
+#pragma unroll
+        for (int j = 0; j < NK; ++j) p[j] = lane_xor_mask<M>(key[NK - 1 - j]);
+#pragma unroll
+        for (int j = 0; j < NK; ++j) key[j] = med3(p[j], key[j], up);
+    }
+    if constexpr (SIZE > 2) sort_halves<NK, SIZE / 4>(key);
+    if constexpr (SIZE < MAX) sort_stages<NK, SIZE * 2, MAX>(key);
 }
 
-// Ascending bitonic sort of 64*NK distinct u32 keys, element e = lane * NK + j
-// in register j of its lane (same network as bitonic_sort), with the lane
-// exchanges of lane_xor (no LDS traffic below lane distance 16) and the stage
-// directions as constant scalar lane masks: a compare-exchange is a lane
-// exchange, one compare and one select.
-template <int NK>
-__device__ __forceinline__ void bitonic_sort32(uint32_t (&key)[NK])
+// Ascending sort of every GROUP (16, 32 or 64) lanes' GROUP * NK u32 keys,
+// element e = lane * NK + j in register j of its lane.  Bitonic network in
+// which every exchange puts the smaller key at the lower index: mirrored first
+// substeps inside a row of 16 lanes, keys complemented in the rows (halves)
+// that have to run down for the stages over 32 and 64 lanes.  Across lanes an
+// exchange is a lane move and a median with the lane's side (distances 16 and
+// 32 by row and half swaps: no LDS traffic), inside a lane a minimum and a
+// maximum: 51 vector instructions for 64 keys, where compares with scalar
+// direction masks and selects took 78 and 63 scalar ones.
+template <int NK, int GROUP = ORBG_WAVE>
+__device__ __forceinline__ void sort32(uint32_t (&key)[NK])
 {
-    bitonic_stage32<NK, 2, ORBG_WAVE * NK>(key);
-}
-
-// One key per lane, the first log2(GROUP) stages of the same network: lanes
-// 0..GROUP-1 end sorted ascending (the following groups alternate direction).
-template <int GROUP>
-__device__ __forceinline__ void bitonic_sort32_groups(uint32_t (&key)[1])
-{
-    bitonic_stage32<1, 2, GROUP>(key);
+    static_assert(GROUP == 16 || GROUP == 32 || GROUP == 64, "lanes of a group");
+    const uint32_t c16 = lane_fill<4>(), c32 = lane_fill<5>();
+    if constexpr (GROUP > 16) {
+#pragma unroll
+        for (int j = 0; j < NK; ++j) key[j] ^= c16;
+    }
+    sort_stages<NK, 2, 16 * NK>(key);
+    if constexpr (GROUP > 16) {
+#pragma unroll
+        for (int j = 0; j < NK; ++j) key[j] ^= GROUP == 64 ? c16 ^ c32 : c16;
+        sort_halves<NK, 16 * NK>(key);
+    }
+    if constexpr (GROUP == 64) {
+#pragma unroll
+        for (int j = 0; j < NK; ++j) key[j] ^= c32;
+        sort_halves<NK, 32 * NK>(key);
+    }
 }
 
 // Ascending sorts of several short sequences at once: groups of LG consecutive
@@ -232,16 +265,6 @@ struct KeyPairU16 {
                                                                       __builtin_bit_cast(u16x2_t, b)));
     }
 };
-
-// Value of lane (lane XOR M), all lanes active.
-template <int M>
-__device__ __forceinline__ uint32_t lane_xor_mask(uint32_t v)
-{
-    if constexpr (M == 3) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x1B, 0xF, 0xF, false);     // quad_perm [3,2,1,0]
-    else if constexpr (M == 7) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);   // row_half_mirror
-    else if constexpr (M == 15) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);  // row_mirror
-    else return lane_xor<M>(v);
-}
 
 // Lanes that hold the lower index of an exchange over lane mask M.
 template <int M>
