@@ -186,8 +186,8 @@ __device__ __forceinline__ uint32_t rank_some(const float (&x)[NK], int n, uint3
 
 // Gauss-Jordan steps on the columns of ranks 1..8 (rank r in lane r - 1 of
 // g[0]), applied to g and to s0 (in a lane of g that holds no rank, or in *sv);
-// returns the mask of independent ranks (bit
-// r - 1), the combinations of the dependent ones in null[0 .. nulls - 1].
+// returns the mask of independent ranks (bit r - 1), the combinations of the
+// dependent ones in null[0 .. nulls - 1].
 // Column k + 1 with a bit outside the pivots so far: bit k of every vector
 // takes one of those bits too if the column's bit k is clear (a row operation;
 // bits at or above n - k start as zero rows), and the column's other bits are
@@ -274,8 +274,8 @@ __device__ __forceinline__ uint32_t match_scan(const uint2* __restrict__ sets, c
 }
 
 // One block: its first member within the budget, written to its outputs.
-template <int NK, bool ORDERED, typename S, class LO>
-__device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t (&hrow)[NK], const CodeDesc& c,
+template <int NK, bool ORDERED, typename S, class CD, class LO>
+__device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t (&hrow)[NK], const CD& c,
                                             const S* __restrict__ cols, MatchLds<S>& L, uint32_t budget,
                                             uint32_t ordv, buf_t cw_row, uint64_t* q_out, uint8_t* ab_out,
                                             float& guess, const LO& lo)
@@ -439,13 +439,24 @@ struct BlockCursor {
     }
 };
 
+// Waves per SIMD the registers are cut for: as many as the search fits without
+// spilling vector registers (left alone it takes 79 at two keys per lane, six
+// waves; at eight waves mixed codes go from 1082 to 990 us, BCH(127,113) 7
+// points from 1999 to 1968; n = 512 loses, 73.8 instead of 72.8 us, and stays).
+template <int NK, bool ORDERED, typename S>
+constexpr int match_waves()
+{
+    const int less = ORDERED ? 1 : 0;
+    return sizeof(S) == 8 ? 1 : NK == 2 ? 8 - less : NK == 4 ? 6 - less : 1;
+}
+
 // One wave per block.  marks (or nullptr): only the blocks marked ORBG_OPEN in
 // the abandon flags.  ids (or nullptr): position i decodes the caller's block
 // ids[i]; ORDERED: with the batch order of row i.  Every lookup uses NK keys
 // per lane (the largest of the launch's codes; keys past a code's length are
 // ranked last).
 template <int NK, bool ORDERED, typename S, bool MIXED>
-__global__ void __launch_bounds__(ORBG_WAVE)
+__global__ void __launch_bounds__(ORBG_WAVE, (match_waves<NK, ORDERED, S>()))
 match_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int64_t* __restrict__ row_off,
              const float* __restrict__ llr, int64_t nblocks, uint32_t budget, const uint8_t* __restrict__ order,
              uint8_t* __restrict__ cw, uint64_t* __restrict__ queries, uint8_t* abandoned, int span,
@@ -498,11 +509,16 @@ match_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     uint64_t hrow0[NK];
     if (HOIST) load_hrows<NK>(s_rows, codes.c[0].m, hrow0);
     float guess = 4.0f;
+    typedef const __attribute__((address_space(4))) CodeTable* const_table_ptr;
+    const_table_ptr table = (const_table_ptr)__builtin_amdgcn_kernarg_segment_ptr();   // `codes`, the first argument
     // the next block's row loads while this one is decoded
     for (;;) {
         b = cur.next();
         fetch(next_in, b);
-        const CodeDesc& c = codes.c[MIXED ? cur_in.ci : 0];
+        // the code's fields are read where they are used (scalar loads): kept in
+        // registers over the loop they spill, and come back by vector instructions
+        asm volatile("" : "+s"(table));
+        const auto& c = table->c[MIXED ? cur_in.ci : 0];
         uint64_t hr[NK];
         if (HOIST) {
 #pragma unroll

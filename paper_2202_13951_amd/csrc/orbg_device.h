@@ -60,7 +60,10 @@ __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 template <int NK, typename KEY = uint64_t>
 __device__ __forceinline__ void bitonic_sort(KEY (&key)[NK])
 {
-    const int lane = lane_id();
+    // the direction masks are made where they are used: hoisted out of a block
+    // loop they take 2 scalar registers each and spill
+    int lane = lane_id();
+    asm volatile("" : "+v"(lane));
 #pragma unroll
     for (int size = 2; size <= ORBG_WAVE * NK; size <<= 1) {
 #pragma unroll
