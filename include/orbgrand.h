@@ -54,10 +54,14 @@ extern "C" {
 /*
  * Launch shape of a decode (the knobs the autotuner sets).  Any field left 0
  * takes the library default (split_steps: -1 takes the default, 0 disables the
- * heavy pass).  Decodes run in two passes: a light pass of persistent
- * one-wave workgroups over all blocks, which gives up on a block after
- * `split_steps` steps of 64 queries, and a heavy pass in which workgroups of
- * `heavy_waves` waves each share one such block, taking its steps in turn.  The
+ * heavy pass).  They shape the search by steps of 64 queries, which decodes the
+ * 1-line order, batch orders of codes with fewer than 9 check bits and codes of
+ * n <= 8: a light pass of persistent one-wave workgroups over all blocks, which
+ * gives up on a block after `split_steps` steps, and a heavy pass in which
+ * workgroups of `heavy_waves` waves each share one such block, taking its steps
+ * in turn.  The other decodes (a search over sets of ranks, which has no long
+ * blocks to split) take their own launch shape; every field is checked all the
+ * same, and one_block_per_workgroup selects the naive launch for them too.  The
  * decoded result does not depend on these values.
  */
 typedef struct orbg_launch_params {
@@ -209,8 +213,7 @@ int orbg_code_release(int code_id);
  * not lie inside both buffers (offset < 0 or offset + n above either length)
  * is read as zeros and its codeword stores are dropped; its queries and flag
  * are still written.  queries/abandoned: DEVICE, one entry per block.
- * Blocks that need many queries move to the heavy pass and are searched by
- * several waves; the result is the same as orbg_decode's for each block.
+ * The result is the same as orbg_decode's for each block.
  * Errors: ORBG_EINVAL for a negative length, and as orbg_decode otherwise.
  */
 int orbg_decode_mixed(const int* codes, int ncodes, const uint8_t* block_code,

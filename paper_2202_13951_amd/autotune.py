@@ -1,6 +1,7 @@
 """Autotuner of the decode launch shape (orbg_launch_params).
 
-Coordinate descent over the five knobs of the persistent two-pass decode:
+Coordinate descent over the five knobs of the persistent two-pass decode (the
+search by steps of the query order; the match search takes its own shape):
 light-pass workgroups per CU, blocks per work-counter increment, the step at
 which a block moves to the heavy pass, waves per heavy block and heavy
 workgroups per CU.  Each candidate is timed with HIP events on the stream the

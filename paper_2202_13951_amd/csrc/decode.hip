@@ -93,8 +93,13 @@ __global__ void __launch_bounds__(256) list_open_kernel(const uint8_t* __restric
     }
 }
 
-// Largest batch that the match search decodes in one launch.
-#define ORBG_MATCH_DIRECT 16384
+// Largest batch that the match search decodes in one launch.  A first pass
+// saves it the short searches, but is a launch of its own, and a wave that takes
+// one block beside the others is as quick as one that takes none.  One launch
+// against two, us: BCH(127,113) at 5 dB 8192 blocks 17.1 / 20.3, 24576 blocks
+// 24.6 / 24.7, 32768 blocks 30.7 / 27.6; n = 256, m = 16 at 24576 blocks 36.9 /
+// 45.8; n = 64, m = 12 19.6 / 23.3; n = 32, m = 6 at 8192 blocks 13.9 / 15.8.
+#define ORBG_MATCH_DIRECT 24576
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream)
 {
@@ -116,8 +121,7 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream)
         }
         return e;
     }
-    // a batch order, or a small batch whose searches are long enough: one launch
-    if (a.order || (a.nblocks <= ORBG_MATCH_DIRECT && many_checks(a))) return launch_match(a, nk, s32, false, stream);
+    if (a.order || a.nblocks <= ORBG_MATCH_DIRECT) return launch_match(a, nk, s32, false, stream);
     // else a first pass (screening and the first batch of patterns), then the
     // match search of the blocks it leaves; at most ORBG_PAST bytes of codewords
     // at a time (the first pass addresses them by 32-bit offsets)

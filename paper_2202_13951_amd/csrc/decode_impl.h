@@ -1,4 +1,7 @@
-// Basic ORBGRAND decode kernels for gfx950.
+// ORBGRAND decode by steps of the query order for gfx950: the 1-line order, batch
+// orders of codes with few check bits, codes of n <= 8, the naive launch and
+// decodes of the first batch alone (list_only).  The other decodes are in
+// match_impl.h and first_impl.h, which share this file's steps 1, 2, 3 and 5.
 //
 // Per block (Algorithm 1 with the basic ORBGRAND generator):
 //   1. stage: the block's LLR row is read coalesced (lane l holds elements
@@ -919,16 +922,16 @@ struct ScreenDepth { static constexpr int value = NKMAX >= 16 ? 1 : 16 / NKMAX; 
 // holds at most 8, 32 per CU), chosen by measurement with 32-bit syndromes:
 // 1 key per lane fits 64 vector registers at 8 waves; 2 keys per lane run
 // best at 7 (at 8 some registers go to scratch, at 6 too few waves hide the
-// latency), except in 1-line mode (no first-batch ranking), which runs best
-// at 8; 4 keys per lane at 6; wider variants keep the compiler's choice.
-template <int NKMAX, typename S, bool ONELINE>
+// latency; 1-line, 10^6 blocks of BCH(127,113) at 5 dB: 633 us at 7, 638 at 6,
+// 648 at 8); 4 keys per lane at 6; wider variants keep the compiler's choice.
+template <int NKMAX, typename S>
 constexpr int light_waves()
 {
-    return sizeof(S) != 4 ? 1 : NKMAX == 1 ? 8 : NKMAX == 2 ? (ONELINE ? 8 : 7) : NKMAX == 4 ? 6 : 1;
+    return sizeof(S) != 4 ? 1 : NKMAX == 1 ? 8 : NKMAX == 2 ? 7 : NKMAX == 4 ? 6 : 1;
 }
 
 template <int NKMAX, bool ORDERED, typename S, bool MIXED, bool ONELINE>
-__global__ void __launch_bounds__(ORBG_WAVE) __attribute__((amdgpu_waves_per_eu(light_waves<NKMAX, S, ONELINE>())))
+__global__ void __launch_bounds__(ORBG_WAVE) __attribute__((amdgpu_waves_per_eu(light_waves<NKMAX, S>())))
 light_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int64_t* __restrict__ row_off,
              const float* __restrict__ llr, int64_t nblocks, uint32_t budget, uint32_t split_steps,
              const uint8_t* __restrict__ order, uint8_t* __restrict__ cw, uint64_t* __restrict__ queries,

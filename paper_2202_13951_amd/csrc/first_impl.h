@@ -13,7 +13,10 @@
 // With c ranks known, the patterns of logistic weight <= c are tested.
 //
 // Bound: vector and scalar issue (each wave instruction holds a SIMD for four
-// cycles) beside the one read of every row.
+// cycles) beside the one read of every row: 48 vector and 49 scalar instructions
+// a block.  7 x 10^6 blocks of BCH(127,113), 4 to 7 dB: 1.23 ms, 3.7 TB/s (a
+// large copy reaches 4.75); with the match search of the 13 % it leaves 1.97 ms,
+// where one pass that ranked and walked block by block took 2.80.
 #pragma once
 #include "match_impl.h"
 

@@ -18,7 +18,9 @@
 //
 // Bound: vector issue; the full sort of a block (56 compare-exchanges of two
 // keys at n = 127) and its fit are a third of the instructions, the search of
-// most blocks takes one or two steps.  Not covered, and left marked in the
+// most blocks takes one or two steps.  10^6 blocks of BCH(127,113) at 5 dB, two
+// lines: 18.0 -> 1.54 ms (the walk of mline_kernel before); 10^5 blocks of n =
+// 256, three lines, 5.5 dB: 38.7 -> 1.07 ms.  Not covered, and left marked in the
 // abandon flag for mline_kernel: results of weight 511 and more, sets of more
 // than seven ranks above 8, sets of two and more with a rank above 254, or past
 // the lists.
@@ -233,11 +235,11 @@ struct MmPattern {
 // One block after its syndrome s0 != 0 is known and its ranks, weights and
 // columns are in LDS.  Returns 0 (not covered), 1 (found) or 2 (no member
 // within the budget).
-template <int NK, typename S, bool WIDE>
+template <int NK, typename S, bool WIDE, class TT>
 struct MmSearch {
     static constexpr uint32_t CAP = mm_cap<WIDE>();
     MmLds<NK, S, WIDE>& L;
-    const MlineSets& T;
+    const TT& T;
     S sv, piv;
     uint32_t nulls, budget;
     S g[NK];                       // columns and weights of ranks lane + 1 + 64 j
@@ -604,8 +606,8 @@ struct MmSearch {
 
 // One block: ranks, fit, search, outputs.  Returns 0 if the search does not cover
 // it (no output but the mark then).
-template <int NK, typename S, bool WIDE>
-__device__ __forceinline__ int mline_match_block(const MlineArgs& a, const MlineSets& T, MmLds<NK, S, WIDE>& L,
+template <int NK, typename S, bool WIDE, class AA, class TT>
+__device__ __forceinline__ int mline_match_block(const AA& a, const TT& T, MmLds<NK, S, WIDE>& L,
                                                  const float (&x)[NK], const uint64_t (&hrow)[NK], int64_t b)
 {
     constexpr uint32_t CAP = mm_cap<WIDE>();
@@ -639,7 +641,7 @@ __device__ __forceinline__ int mline_match_block(const MlineArgs& a, const Mline
         j0v = md.J[0];
         if (s0 != 0) {
             const uint32_t limit = (n < 32 && a.budget > (1u << n)) ? (1u << n) : a.budget;
-            MmSearch<NK, S, WIDE> F{L, T, s0, 0, 0u, limit, {}, {}, 0u, 0u};
+            MmSearch<NK, S, WIDE, TT> F{L, T, s0, 0, 0u, limit, {}, {}, 0u, 0u};
             // weight of rank r, cut at the cap (ranks past n weigh that much)
             auto weigh = [&](int r, MmSplit& sp) -> uint32_t {
                 int J = md.J[0], B = md.B[0], I = 0, s = 0;
@@ -750,7 +752,7 @@ __device__ __forceinline__ int mline_match_block(const MlineArgs& a, const Mline
 }
 
 template <int NK, typename S>
-__global__ void __launch_bounds__(ORBG_WAVE) mline_match_kernel(MlineArgs a)
+__global__ void __launch_bounds__(ORBG_WAVE, NK <= 2 ? 4 : 1) mline_match_kernel(MlineArgs a)
 {
     __shared__ MmLds<NK, S, false> L;
     const int lane = lane_id();
@@ -761,12 +763,17 @@ __global__ void __launch_bounds__(ORBG_WAVE) mline_match_kernel(MlineArgs a)
     auto fetch = [&](float (&x)[NK], int64_t b) {
         load_row_buf<NK>(make_buf(a.llr + (b < a.nblocks ? b * (int64_t)n : 0), b < a.nblocks ? (uint32_t)n * 4u : 0u), x);
     };
+    typedef const __attribute__((address_space(4))) MlineArgs* const_args_ptr;
+    const_args_ptr args = (const_args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
     float x[NK], next[NK];
     int64_t b = blockIdx.x;
     fetch(x, b);
     while (b < a.nblocks) {
         fetch(next, b + gridDim.x);                       // loads while this block is decoded
-        mline_match_block<NK, S, false>(a, a.sets, L, x, hrow, b);
+        // the arguments are read where they are used (scalar loads): kept in
+        // registers over the loop they spill, and come back by vector instructions
+        asm volatile("" : "+s"(args));
+        mline_match_block<NK, S, false>(*args, args->sets, L, x, hrow, b);
         b += gridDim.x;
 #pragma unroll
         for (int j = 0; j < NK; ++j) x[j] = next[j];

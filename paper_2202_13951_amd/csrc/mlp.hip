@@ -547,6 +547,8 @@ mlp_infer_persistent(const float* __restrict__ llr, int64_t llr_rows, const int6
     }
 }
 
+// Rows from which the persistent kernel is the quicker one (20000 rows 29.0 us
+// against 27.2 of the other, 32768 rows 27.9 against 32).
 #define MLP_PERSIST_ROWS 24576
 hipError_t mlp_infer(const float* w, const uint16_t* wb, const float* llr, int64_t llr_rows, const int64_t* ids,
                      const uint16_t* x, int64_t batch, float* logits, uint8_t* order, bool pin0, hipStream_t st)

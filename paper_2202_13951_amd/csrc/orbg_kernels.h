@@ -4,7 +4,7 @@
 #include <stdint.h>
 
 #define ORBG_MAX_CODES 8       // codes one launch may mix
-#define ORBG_MATCH_M 10        // check bits from which a search rarely ends in its first steps
+#define ORBG_MATCH_M 9         // check bits from which an ordered search rarely ends in its first steps
 #define ORBG_MIXED_COLS 2048   // packed columns of all codes of a mixed launch (sum of n)
 
 namespace orbg {
@@ -37,7 +37,7 @@ struct CodeTable {
     CodeDesc c[ORBG_MAX_CODES];
 };
 
-// Launch shape (the autotuner's knobs).
+// Launch shape (the autotuner's knobs) of the search by steps.
 struct LaunchParams {
     int wg_per_cu;             // light pass: one-wave workgroups per compute unit
     int chunk;                 // blocks per work-counter increment (0 = about 16 per wave)
@@ -91,7 +91,9 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 // The match search decodes every code that has its tables, but not the 1-line
 // order, nor where the first batch alone or the naive launch is asked for; with
 // a batch order it takes codes of ORBG_MATCH_M check bits or more (with fewer,
-// 4096 patterns hold many members, and the first steps of the order find one).
+// 4096 patterns hold many members, and the first steps of the order find one:
+// 30000 blocks of n = 64 at 4 dB, us with the match search / by steps: m = 8
+// 131 / 100, m = 9 82 / 104, m = 10 60 / 109, m = 12 40 / 121).
 inline bool many_checks(const DecodeArgs& a)
 {
     for (int i = 0; i < a.codes.ncodes; ++i)

@@ -15,7 +15,7 @@ from synth import channel, codes
 
 pytestmark = pytest.mark.gpu
 THREADS = min(16, os.cpu_count() or 1)
-DIRECT = 16384                       # largest batch decoded by one launch
+DIRECT = 24576                       # largest batch decoded by one launch
 
 
 def _check(got, want, tag):
@@ -173,3 +173,14 @@ def test_more_codewords_than_one_launch_addresses(gpu_device):
     half = blocks // 2 + 1
     for got, a, b in zip(whole, binding.orbg_decode(H, llr[:half], budget), binding.orbg_decode(H, llr[half:], budget)):
         assert torch.equal(got[:half], a) and torch.equal(got[half:], b)
+
+
+@pytest.mark.parametrize("m", [8, 9])
+def test_batch_orders_of_few_check_bits(gpu_device, m):
+    """Both sides of the rule that sends an ordered decode to the match search."""
+    print(f"match order m={m}", flush=True)
+    H = codes.rlc_H(64, 64 - m, seed=m)
+    llr, _ = channel.awgn_llr(codes.generator_matrix(H), 300, 3.0, seed=m)
+    order = np.stack([np.random.default_rng(b).permutation(64) for b in range(300)]).astype(np.uint8)
+    got = binding.orbg_decode_ordered(H, torch.from_numpy(llr).to(gpu_device), 6000, torch.from_numpy(order).to(gpu_device))
+    _check(got, O.decode_ordered(H, llr, 6000, order, THREADS), f"order m={m}")
