@@ -13,9 +13,9 @@
 // With c ranks known, the patterns of logistic weight <= c are tested.
 //
 // Bound: vector and scalar issue (each wave instruction holds a SIMD for four
-// cycles) beside the one read of every row: 48 vector and 49 scalar instructions
-// a block.  7 x 10^6 blocks of BCH(127,113), 4 to 7 dB: 1.23 ms, 3.7 TB/s (a
-// large copy reaches 4.75); with the match search of the 13 % it leaves 1.97 ms,
+// cycles) beside the one read of every row: 47 vector and 45 scalar instructions
+// a block.  7 x 10^6 blocks of BCH(127,113), 4 to 7 dB: 1.21 ms, 3.9 TB/s (a
+// large copy reaches 4.75); with the match search of the 14 % it leaves 1.97 ms,
 // where one pass that ranked and walked block by block took 2.80.
 #pragma once
 #include "match_impl.h"
@@ -24,23 +24,28 @@ namespace orbg {
 
 #define ORBG_FIRST_MIN 9         // fewest ranks a block goes on with
 #define ORBG_FIRST_N 12          // shorter codes go to the match search
-#define ORBG_FIRST_SLOTS 32      // staged blocks: at most 3 left over and 16 of one group (a power of two)
 #define ORBG_FIRST_ROW 20        // ranks 0..16 of a sorted block, padded
 
+// Staged blocks: at most 3 left over and the K (<= 16) of one group; a power of two.
+constexpr uint32_t first_slots(int k) { return k <= 4 ? 8u : k <= 8 ? 16u : 32u; }
+
 // Words of a staged block: its hard decision (2 NK), syndrome (2), index and
-// (ranks | code << 8); one per lane of the store, so a power of two.
-template <int NK>
+// (ranks | code << 8), mixed codes also the row's offset (2) and length; one per
+// lane of the store, so a power of two.
+template <int NK, bool MIXED>
 struct FirstWords {
-    static constexpr int SYN = 2 * NK, ID = 2 * NK + 2, INFO = 2 * NK + 3;
-    static constexpr int W = NK <= 2 ? 8 : NK == 4 ? 16 : NK == 8 ? 32 : 64;
+    static constexpr int SYN = 2 * NK, ID = 2 * NK + 2, INFO = 2 * NK + 3, ROW = 2 * NK + 4, LEN = 2 * NK + 6;
+    static constexpr int W = NK <= 2 && !MIXED ? 8 : NK <= 4 ? 16 : NK == 8 ? 32 : 64;
 };
 
-template <int NK, typename S>
+template <int NK, typename S, bool MIXED, int K>
 struct FirstLds {
-    uint32_t key[ORBG_FIRST_SLOTS * 16];
-    uint32_t word[ORBG_FIRST_SLOTS * FirstWords<NK>::W + ORBG_WAVE];   // (the last 64: lanes past W)
+    static constexpr uint32_t SLOTS = first_slots(K);
+    uint32_t key[SLOTS * 16];
+    uint32_t word[SLOTS * FirstWords<NK, MIXED>::W + ORBG_WAVE];   // (the last 64: lanes past W)
     S h[4 * ORBG_FIRST_ROW];             // columns by rank of four sorted blocks (rank 0: zero)
     uint32_t pi[4 * ORBG_FIRST_ROW];     // their received indices (rank 0: none)
+    uint4 code[MIXED ? ORBG_MAX_CODES : 1];   // mixed codes: n, m | nk << 8, row_base, col_base
 };
 
 // Lane l of `reg` <- v (both wave-uniform).  (clang has no builtin for it; the
@@ -61,7 +66,8 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     extern __shared__ __align__(16) unsigned char orbg_dyn_lds[];
     uint64_t* s_rows = reinterpret_cast<uint64_t*>(orbg_dyn_lds);
     S* s_cols = reinterpret_cast<S*>(orbg_dyn_lds + (size_t)codes.rwords * sizeof(uint64_t));
-    __shared__ FirstLds<NK, S> L;
+    __shared__ FirstLds<NK, S, MIXED, K> L;
+    constexpr uint32_t SLOTS = first_slots(K);
     constexpr int IB = IndexBits<NK>::value;
     constexpr bool HOIST = !MIXED && NK <= 4;
     const int lane = lane_id();
@@ -69,6 +75,7 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
         const CodeDesc& c = codes.c[ci];
         for (int i = threadIdx.x; i < c.n; i += ORBG_WAVE) s_cols[c.col_base + i] = (S)c.cols[i];
         for (int i = threadIdx.x; i < c.m * c.nk; i += ORBG_WAVE) s_rows[c.row_base + i] = c.rows[i];
+        if (MIXED && lane == 0) L.code[ci] = make_uint4((uint32_t)c.n, (uint32_t)(c.m | c.nk << 8), c.row_base, c.col_base);
     }
     if (lane < 4) {
         L.h[lane * ORBG_FIRST_ROW] = 0;
@@ -96,9 +103,9 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     if (HOIST) load_hrows<NK>(s_rows, codes.c[0].m, hrow0);
     LaneOffs<NK> lo = lane_offsets<NK>(MIXED ? NK * ORBG_WAVE : codes.c[0].n);
 
-    using Q = FirstWords<NK>;
+    using Q = FirstWords<NK, MIXED>;
     // this lane's word of slot 0; lanes past W write beside the slots
-    uint32_t* const my_word = &L.word[lane < Q::W ? lane : ORBG_FIRST_SLOTS * Q::W + lane];
+    uint32_t* const my_word = &L.word[lane < Q::W ? lane : SLOTS * Q::W + lane];
     const uint32_t word_step = lane < Q::W ? Q::W : 0u;
     // one code: codewords, query counts and flags of all blocks (the host keeps
     // the batch's codewords within ORBG_PAST bytes); a block is a scalar offset
@@ -109,16 +116,9 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     uint32_t head = 0, staged = 0;
     float tau = 2.0f;                                     // threshold, carried from block to block
 
-    auto row_of = [&](int64_t b, int& ci) -> int64_t {
-        ci = 0;
-        if (!MIXED) return b * codes.c[0].n;
-        ci = (int)scalar_load_u8(block_code, b);
-        ci = ci < codes.ncodes ? ci : 0;                  // out-of-range indices read code 0
-        const int64_t row = scalar_load_i64(row_off, b);
-        return uniform_i64((row >= 0 && row <= row_limit - codes.c[ci].n) ? row : -1);
-    };
     // codeword y, query count and flag of block b
-    auto write = [&](uint32_t b, int ci, int64_t row, const uint64_t (&y)[NK], uint32_t q) {
+    // (mixed codes: its row's offset, or -1, and length)
+    auto write = [&](uint32_t b, int64_t row, uint32_t n, const uint64_t (&y)[NK], uint32_t q) {
         const u32x2_t qv = {q, 0u};
         if constexpr (!MIXED) {
 #pragma unroll
@@ -128,7 +128,7 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
             __builtin_amdgcn_raw_buffer_store_b64(qv, q_all, lo.r, b * 8u, 0);
             __builtin_amdgcn_raw_buffer_store_b8((uint8_t)0, ab_all, lo.r, b, 0);
         } else {
-            const buf_t cb = make_buf(cw + (row >= 0 ? row : 0), row >= 0 ? (uint32_t)codes.c[ci].n : 0u);
+            const buf_t cb = make_buf(cw + (row >= 0 ? row : 0), row >= 0 ? n : 0u);
 #pragma unroll
             for (int j = 0; j < NK; ++j)
                 __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(__builtin_amdgcn_inverse_ballot_w64(y[j]) ? 1 : 0), cb,
@@ -144,23 +144,20 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     // Sorts the `cnt` (1..4) oldest staged blocks and tests their patterns.
     auto flush = [&](uint32_t cnt) {
         const uint32_t sub = (uint32_t)lane >> 4, in = (uint32_t)lane & 15u;
-        const uint32_t slot = (head + sub) & (ORBG_FIRST_SLOTS - 1);
+        const uint32_t slot = (head + sub) & (SLOTS - 1);
         wave_lds_sync();
         const uint32_t mt = L.word[slot * Q::W + Q::INFO];
         uint32_t words[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            words[j] = L.word[((head + (uint32_t)j) & (ORBG_FIRST_SLOTS - 1)) * Q::W + ((uint32_t)lane & (Q::W - 1))];
+            words[j] = L.word[((head + (uint32_t)j) & (SLOTS - 1)) * Q::W + ((uint32_t)lane & (Q::W - 1))];
         const uint32_t known = sub < cnt ? mt & 0xffu : 0u;
         uint32_t k1[1] = {in < known ? L.key[slot * 16u + in] : 0xffffffffu};
         sort32<1, 16>(k1);
         const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)k1[0], 0x101, 0xF, 0xF, false);   // row_shl:1
         const uint64_t ties = ballot(in + 1u < known && ((k1[0] ^ next) >> IB) == 0u);
         const uint32_t idx = k1[0] & ((1u << IB) - 1u);
-        const uint32_t base = MIXED ? (uint32_t)codes.c[0].col_base : 0u;
-        uint32_t cb = base;
-        if (MIXED)
-            for (int ci = 1; ci < codes.ncodes; ++ci) cb = (mt >> 8) == (uint32_t)ci ? codes.c[ci].col_base : cb;
+        const uint32_t cb = MIXED ? (sub < cnt ? L.code[mt >> 8].w : 0u) : 0u;
         const S col = s_cols[in < known ? cb + idx : 0u];
         L.h[sub * ORBG_FIRST_ROW + 1 + in] = in < known ? col : (S)0;
         L.pi[sub * ORBG_FIRST_ROW + 1 + in] = in < known ? idx : ~0u;
@@ -189,23 +186,40 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
 #pragma unroll
                     for (int k = 0; k < NK; ++k) y[k] ^= ballot((uint32_t)(k * ORBG_WAVE + lane) == p);
                 }
-                int ci = 0;
-                const int64_t row = MIXED ? row_of(b, ci) : 0;
-                write(b, ci, row, y, wl + 1u);
+                if constexpr (MIXED)
+                    write(b, (int64_t)(((uint64_t)get(Q::ROW + 1) << 32) | get(Q::ROW)), get(Q::LEN), y, wl + 1u);
+                else
+                    write(b, 0, 0u, y, wl + 1u);
             } else {
                 mark(b);
             }
         }
         wave_lds_sync();
-        head = (head + cnt) & (ORBG_FIRST_SLOTS - 1);
+        head = (head + cnt) & (SLOTS - 1);
         staged -= cnt;
     };
 
     const int64_t step = (int64_t)gridDim.x * K;
+    // mixed codes: lane l loads the code and row offset of the group's block l, one
+    // group early (scalar loads, three round trips in a row for each block, took
+    // three codes' 10^6 blocks from 901 to 991 us a decode)
+    uint32_t code_in = 0;
+    int64_t row_in = -1;
+    auto ahead = [&](int64_t g) {
+        const bool in = MIXED && lane < K && g + lane < nblocks;
+        code_in = in ? block_code[g + lane] : 0u;
+        row_in = in ? row_off[g + lane] : -1;
+    };
+    if (MIXED) ahead((int64_t)blockIdx.x * K);
     for (int64_t g = (int64_t)blockIdx.x * K; g < nblocks; g += step) {
         float xs[K][NK];
-        int64_t rows[K];
-        int cis[K];
+        uint4 code = {0u, 0u, 0u, 0u};                    // lane l: block l's
+        uint32_t code_id = 0;
+        int64_t row_id = -1;
+        auto of = [&](uint32_t v, int kk) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)v, kk); };
+        auto row_at = [&](int kk) -> int64_t {
+            return (int64_t)(((uint64_t)of((uint32_t)((uint64_t)row_id >> 32), kk) << 32) | of((uint32_t)row_id, kk));
+        };
         const uint32_t cnt = uniform_u32((uint32_t)(nblocks - g < K ? nblocks - g : K));
         if constexpr (!MIXED) {
             // the group's rows lie back to back: one descriptor, a scalar offset per row
@@ -214,13 +228,14 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
 #pragma unroll
             for (int kk = 0; kk < K; ++kk) load_row_buf<NK>(lb, xs[kk], lo, (uint32_t)kk < cnt ? (uint32_t)kk * n4 : 0u);
         } else {
+            code_id = code_in < (uint32_t)codes.ncodes ? code_in : 0u;   // out-of-range indices read code 0
+            code = L.code[code_id];
+            row_id = row_in >= 0 && row_in <= row_limit - (int64_t)code.x ? row_in : -1;
+            ahead(g + step);
 #pragma unroll
             for (int kk = 0; kk < K; ++kk) {
-                cis[kk] = 0;
-                rows[kk] = (uint32_t)kk < cnt ? row_of(g + kk, cis[kk]) : -1;
-                const bool rv = rows[kk] >= 0;
-                load_row_buf<NK>(make_buf(llr + (rv ? rows[kk] : 0), rv ? (uint32_t)codes.c[cis[kk]].n * 4u : 0u), xs[kk],
-                                 lo);
+                const int64_t row = row_at(kk);
+                load_row_buf<NK>(make_buf(llr + (row >= 0 ? row : 0), row >= 0 ? of(code.x, kk) * 4u : 0u), xs[kk], lo);
             }
         }
         int64_t g2 = g;
@@ -229,22 +244,22 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
 #pragma unroll
         for (int kk = 0; kk < K; ++kk) {
             if ((uint32_t)kk >= cnt2) break;
-            const int ci = MIXED ? cis[kk] : 0;
-            const CodeDesc& c = codes.c[ci];
+            const uint32_t n = MIXED ? of(code.x, kk) : (uint32_t)codes.c[0].n;
             uint64_t hr[NK];
             if (HOIST) {
 #pragma unroll
                 for (int j = 0; j < NK; ++j) hr[j] = hrow0[j];
             } else {
-                load_hrows_pad<NK>(s_rows + c.row_base, c.m, c.nk, hr);
+                const uint32_t mk = MIXED ? of(code.y, kk) : (uint32_t)(codes.c[0].m | codes.c[0].nk << 8);
+                load_hrows_pad<NK>(s_rows + (MIXED ? of(code.z, kk) : 0u), (int)(mk & 0xffu), (int)(mk >> 8), hr);
             }
             bool yb[NK];
-            const S s0 = hard_decision<NK, S>(xs[kk], c.n, hr, yb);
+            const S s0 = hard_decision<NK, S>(xs[kk], (int)n, hr, yb);
             uint64_t y[NK];
 #pragma unroll
             for (int j = 0; j < NK; ++j) y[j] = ballot(yb[j]);
             if (s0 == 0) {
-                write((uint32_t)g2 + kk, ci, MIXED ? rows[kk] : 0, y, 1u);
+                write((uint32_t)g2 + kk, MIXED ? row_at(kk) : 0, n, y, 1u);
                 continue;
             }
             // threshold: 9 to 16 magnitudes below it, by steps of a quarter and
@@ -257,8 +272,8 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
                 for (int j = 0; j < NK; ++j) {
                     // lanes past n read 0 and are no candidates
                     mk[j] = ballot(fabsf(xs[kk][j]) < tau) &
-                            (c.n >= (j + 1) * ORBG_WAVE ? ~0ull : c.n <= j * ORBG_WAVE ? 0ull
-                                                                                    : (1ull << (c.n & 63)) - 1ull);
+                            ((int)n >= (j + 1) * ORBG_WAVE ? ~0ull : (int)n <= j * ORBG_WAVE ? 0ull
+                                                                                     : (1ull << (n & 63u)) - 1ull);
                     below += (uint32_t)__builtin_popcountll(mk[j]);
                 }
             };
@@ -274,11 +289,11 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
                 const float mid = 0.5f * (lo_t + hi_t);
                 tau = __uint_as_float(uniform_u32(__float_as_uint(lo_t == 0.0f || hi_t == 0.0f ? open : mid)));
             }
-            if (below < ORBG_FIRST_MIN || below > 16u || c.n < ORBG_FIRST_N) {
+            if (below < ORBG_FIRST_MIN || below > 16u || n < ORBG_FIRST_N) {
                 mark((uint32_t)g2 + kk);
                 continue;
             }
-            const uint32_t slot = (head + staged) & (ORBG_FIRST_SLOTS - 1);
+            const uint32_t slot = (head + staged) & (SLOTS - 1);
             uint32_t at = slot * 16u;
 #pragma unroll
             for (int j = 0; j < NK; ++j) {
@@ -299,7 +314,13 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
             writelane(wv, (uint32_t)s0, Q::SYN);
             if (sizeof(S) == 8) writelane(wv, (uint32_t)((uint64_t)s0 >> 32), Q::SYN + 1);
             writelane(wv, (uint32_t)g2 + kk, Q::ID);
-            writelane(wv, below | ((uint32_t)ci << 8), Q::INFO);
+            writelane(wv, below | (MIXED ? of(code_id, kk) << 8 : 0u), Q::INFO);
+            if (MIXED) {
+                const int64_t row = row_at(kk);
+                writelane(wv, (uint32_t)row, Q::ROW);
+                writelane(wv, (uint32_t)((uint64_t)row >> 32), Q::ROW + 1);
+                writelane(wv, n, Q::LEN);
+            }
             my_word[slot * word_step] = wv;
             ++staged;
         }

@@ -26,8 +26,8 @@
 // BCH(127,113) at 4 dB, 10^5 queries at most, 443 -> 135 us a batch (with the
 // first pass); n = 512, m = 20, 5 x 10^6 queries, 1006 -> 73 us; three codes
 // mixed, 10^6 blocks, 4.2 -> 0.98 ms; 10^4 blocks of n = 32, m = 6, 41 -> 13 us.
-// About 410 vector and 360 scalar instructions a block, 64 % of the vector
-// issue rate.
+// About 345 vector and as many scalar instructions a block, 69 % of the issue
+// rate of each.
 #pragma once
 #include "decode_impl.h"
 
