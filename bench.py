@@ -376,7 +376,7 @@ def run_single(args, wl, dev):
         "roofline": {"bound": "alu", "achieved": ops / kavg / 1e12, "peak": PEAK_INT32_OPS / 1e12,
                      "unit": "Tops/s (int32)", "frac": ops / kavg / PEAK_INT32_OPS,
                      "traffic": profiled_traffic(args.workload),
-                     "kernel": "light_kernel + heavy_kernel (one decode call)", "ops_per_launch": ops,
+                     "kernel": "first_kernel + match_kernel (one decode call)", "ops_per_launch": ops,
                      "hbm": {"achieved_GBps": hbm_bytes / kavg / 1e9, "peak_GBps": PEAK_HBM / 1e9,
                              "frac": hbm_bytes / kavg / PEAK_HBM, "bytes_per_launch": hbm_bytes}},
     }
@@ -608,7 +608,7 @@ def run_mixed(args, wl, dev):
         "roofline": {"bound": "alu", "achieved": ops_tot / ksec / 1e12, "peak": PEAK_INT32_OPS / 1e12,
                      "unit": "Tops/s (int32)", "frac": ops_tot / ksec / PEAK_INT32_OPS,
                      "traffic": profiled_traffic(args.workload) if not args.ebn0 else None,
-                     "kernel": "light_kernel<4> + heavy_kernel (one mixed decode call per point)",
+                     "kernel": "first_kernel<4> + match_kernel<4> (one mixed decode call per point)",
                      "ops_per_launch": ops_tot / len(wl["ebn0"]),
                      "hbm": {"achieved_GBps": bytes_tot / ksec / 1e9, "peak_GBps": PEAK_HBM / 1e9,
                              "frac": bytes_tot / ksec / PEAK_HBM, "bytes_per_launch": bytes_tot / len(wl["ebn0"])}},
@@ -920,7 +920,7 @@ def run_learned(args, wl, dev):
         "mean_queries_prior_order": tot_q["prior"] / Nt,
         "roofline": {"bound": "mfma", "achieved": mfma / 1e12, "peak": 2500.0, "unit": "TFLOP/s (bf16)",
                      "frac": mfma / 2.5e15, "traffic": None,
-                     "kernel": "mlp_infer_kernel (fused three-layer forward, activations in LDS)",
+                     "kernel": "mlp_infer_persistent (fused three-layer forward, weights in registers)",
                      "flop_per_launch": flops_fwd * fwd_rows / max(len(wl["ebn0"]), 1)},
         "pair_generation_s": gen_s, "blocks_decoded_for_pairs": seen, "training_s": train_s,
         "train_loss_per_epoch": losses, "label_entropy_nats": label_entropy, "per_point": points,
@@ -1049,7 +1049,7 @@ def run_mline(args, wl, dev):
                      # counters were taken for the workload's own line count
                      "traffic": (profiled_traffic(args.workload, "mline_kernel", MLINE_SOURCES)
                                  if segments == wl["segments"] else None),
-                     "kernel": "mline_kernel (one decode call)", "ops_per_launch": ops,
+                     "kernel": "mline_match_kernel + mline_kernel (one decode call)", "ops_per_launch": ops,
                      "hbm": {"achieved_GBps": hbm_bytes / kavg / 1e9, "peak_GBps": PEAK_HBM / 1e9,
                              "frac": hbm_bytes / kavg / PEAK_HBM, "bytes_per_launch": hbm_bytes}},
     }
