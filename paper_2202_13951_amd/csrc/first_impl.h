@@ -290,6 +290,7 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
                 tau = __uint_as_float(uniform_u32(__float_as_uint(lo_t == 0.0f || hi_t == 0.0f ? open : mid)));
             }
             if (below < ORBG_FIRST_MIN || below > 16u || n < ORBG_FIRST_N) {
+                tau = tau > 0.0f && tau < INFINITY ? tau : 2.0f;   // (rows of zeros or infinities)
                 mark((uint32_t)g2 + kk);
                 continue;
             }

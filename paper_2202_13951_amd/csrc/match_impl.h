@@ -17,15 +17,15 @@
 // Bound: the search is short (1 to 4 steps for most blocks), so a block's time
 // is its ranking and the latency of a chain of a few table reads.  The ranking
 // is therefore partial: patterns of logistic weight <= R flip ranks <= R only,
-// so the 44 to 64 least reliable ranks, found with a threshold and sorted one
+// so the 44 to 63 least reliable ranks, found with a threshold and sorted one
 // key per lane (21 substeps), serve every weight up to their number (10^4
 // patterns and more), and the whole block is sorted (28 substeps of two keys
 // at n = 127, 45 of eight at n = 512) only when the search goes past it.
 //
 // Measured, the walk of the order (light and heavy pass) against this search:
-// BCH(127,113) at 4 dB, 10^5 queries at most, 443 -> 135 us a batch (with the
-// first pass); n = 512, m = 20, 5 x 10^6 queries, 1006 -> 73 us; three codes
-// mixed, 10^6 blocks, 4.2 -> 0.98 ms; 10^4 blocks of n = 32, m = 6, 41 -> 13 us.
+// 2 x 10^5 blocks of BCH(127,113) at 4 dB, 10^5 queries, 443 -> 135 us (with the
+// first pass); 5003 blocks of n = 512, m = 22, 10^6 queries, 1006 -> 73 us;
+// three codes mixed, 10^6 blocks, 4.3 -> 0.90 ms; 10^4 blocks of n = 32, m = 6, 41 -> 13 us.
 // About 345 vector and as many scalar instructions a block, 69 % of the issue
 // rate of each.
 #pragma once
@@ -33,7 +33,7 @@
 
 namespace orbg {
 
-#define ORBG_MATCH_SOME 44       // fewest ranks of a partial ranking (at most 64), where the limit needs as many
+#define ORBG_MATCH_SOME 44       // fewest ranks of a partial ranking (at most 63), where the limit needs as many
 
 template <typename S>
 struct MatchLds {
