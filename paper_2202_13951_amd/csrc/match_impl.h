@@ -393,7 +393,9 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
         if (q > lim) q = 0;
     }
     uint32_t win_lo = 0, win_hi = 0;
-    if (q > 1) {                                          // as a schedule entry: byte 0 the mask, then the ranks
+    // a pattern was found (a batch order can make any pattern query 1, not only the
+    // empty one): as a schedule entry, byte 0 the mask, then the ranks
+    if (q != 0 && best.x != ~0u) {
         win_lo = pattern_mask(best) | ((best.x >> 16) & 0xff00u) | (best.x & 0xff0000u) | (best.x << 16 & 0xff000000u);
         win_hi = (best.x & 0xffu) | ((best.y >> 16) & 0xff00u) | (best.y & 0xff0000u) | (best.y << 16 & 0xff000000u);
     }
