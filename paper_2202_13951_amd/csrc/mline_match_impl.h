@@ -65,9 +65,11 @@ __device__ __forceinline__ MmSplitLds<WIDE> put_split(const MmSplit& p)
 }
 
 // Ranks that the sets of two ranks and more can hold, by the code's width.  The
-// slot after the last one is the end marks' rank, and that of single ranks past
-// it: pattern bytes (255, then the rank - 255 in the last byte), ORBG_MM_SINGLE
-// being the largest.
+// slot after the last one is the end marks' rank.  Single ranks past it have the
+// pattern bytes (255, then the rank - 255 in the last byte), ORBG_MM_SINGLE being
+// the largest.  Those from 256 on lie in the last segment (its first rank is at
+// most 256: anchors but the last are below floor(n / 2) <= 256) and share a
+// split; rank 255 may end the segment before and has its own.
 #define ORBG_MM_SINGLE 510
 template <int NK>
 constexpr int mm_ranks() { return NK <= 2 ? ORBG_MATCH_RANKS : ORBG_MM_RANKS; }
@@ -76,7 +78,7 @@ template <int NK, typename S, bool WIDE>
 struct MmLds {
     struct Rank { S h; uint32_t v; };
     Rank r[mm_ranks<NK>() + 2];            // transformed column and weight of rank r (0: none)
-    MmSplitLds<WIDE> split[mm_ranks<NK>() + 2];   // of rank r alone
+    MmSplitLds<WIDE> split[mm_ranks<NK>() + 3];   // of rank r alone (single ranks: slots 255 and 256)
     struct { uint32_t v; MmSplitLds<WIDE> split; } nib[32];   // subsets of ranks 1..4 and 5..8
     union {
         uint32_t hist[ORBG_MM_HIST];    // narrow: hist[w] = subsets of ranks 1..8 of weight <= w;
@@ -342,7 +344,10 @@ struct MmSearch {
     {
         MmSplit p = mask_split(m);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) p = p + get_split<WIDE>(L.split[(x >> (24 - 8 * k)) & 0xffu]);
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t r = (x >> (24 - 8 * k)) & 0xffu;
+            p = p + get_split<WIDE>(L.split[NK >= 4 && k == 0 && (y & 0xffu) != 0 ? r + 1u : r]);
+        }
         if (ballot(y != 0u) != 0ull) {
 #pragma unroll
             for (int k = 0; k < 3; ++k) p = p + get_split<WIDE>(L.split[(y >> (24 - 8 * k)) & 0xffu]);
@@ -434,8 +439,8 @@ struct MmSearch {
         }
     }
 
-    // f(x, y, weight, column, rank) for the empty set (lane 0 of the first step)
-    // and the single ranks above 8; weight ~0 where a lane holds neither.
+    // f(x, y, weight, column, slot of its split) for the empty set (lane 0 of the
+    // first step) and the single ranks above 8; weight ~0 where a lane holds neither.
     template <typename F>
     __device__ __forceinline__ void each_single(F&& f) const
     {
@@ -446,7 +451,8 @@ struct MmSearch {
             const bool low = j == 0 && r <= ORBG_LOW_RANKS, far = NK >= 4 && r > ORBG_MM_RANKS;
             const uint32_t wu = low ? (lane == 0 ? 0u : ~0u) : (NK < 8 || r <= ORBG_MM_SINGLE) ? vr[j] : ~0u;
             f(low ? 0u : far ? (uint32_t)(ORBG_MM_RANKS + 1) << 24 : r << 24,
-              far ? r - (ORBG_MM_RANKS + 1) : 0u, wu, low ? (S)0 : g[j], low ? 0u : far ? (uint32_t)(ORBG_MM_RANKS + 1) : r);
+              far ? r - (ORBG_MM_RANKS + 1) : 0u, wu, low ? (S)0 : g[j],
+              low ? 0u : r < ORBG_MM_RANKS + 2u || !far ? r : ORBG_MM_RANKS + 2u);
         }
     }
 
@@ -676,13 +682,15 @@ __device__ __forceinline__ int mline_match_block(const AA& a, const TT& T, MmLds
                 if (r <= RANKS) {
                     L.r[r] = {F.g[j], F.vr[j]};
                     L.split[r] = put_split<WIDE>(sp[j]);
+                } else if (NK >= 4 && r == RANKS + 1) {
+                    L.split[r] = put_split<WIDE>(sp[j]);
                 }
             }
             if (lane == 0) {
                 L.r[0] = {0, 0u};
                 L.split[0] = {};
                 L.r[RANKS + 1] = {0, CAP};
-                L.split[RANKS + 1] = put_split<WIDE>({0u, 0u, 0u, 1u << (8 * (md.m - 1))});   // (single ranks past)
+                if (NK >= 4) L.split[RANKS + 2] = put_split<WIDE>({0u, 0u, 0u, 1u << (8 * (md.m - 1))});
             }
             // subsets of ranks 1..4 (lanes 0..15) and 5..8 (lanes 16..31)
             uint32_t nv = 0;

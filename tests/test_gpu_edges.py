@@ -1,5 +1,6 @@
 """GPU parity with the CPU oracle, bit for bit, at edges of the match searches and
-of the passes in front of them: results at the first position of a batch order."""
+of the passes in front of them: results at the first position of a batch order,
+ranks past those that the m-line search's sets hold."""
 import os
 
 import numpy as np
@@ -44,3 +45,67 @@ def test_first_query_of_a_batch_order(gpu_device, n, m, budget):
     want = O.decode_ordered(H, llr, budget, order, THREADS)
     assert (want[1] == 1).all() and (want[0] == cw).all()
     _check(got, want, f"order n={n} budget={budget}")
+
+
+def _mline(dev, H, llr, budget, segments, tag, jdiv=False):
+    got = binding.orbg_decode_mline(H, torch.from_numpy(llr).to(dev), budget, segments, jdiv=jdiv)
+    want = O.decode_mline(H, llr, budget, segments, jdiv=jdiv, threads=THREADS)
+    _check(got[:3], want[:3], tag)
+    assert (got[3].cpu().numpy() == want[3]).all()
+    return want
+
+
+@pytest.mark.parametrize("both", [False, True])
+def test_mline_rank_255_ends_a_segment(gpu_device, both):
+    """n = 512: an anchor at rank 255 puts that rank, a single one past those that
+    the sets hold, in the last segment but one.  Ranks are the indices; {1, 2, 255}
+    and {3, 21, 54} weigh the same; `both`: one is a member where the other is."""
+    print(f"mline rank 255 three lines both={both}", flush=True)
+    n, m = 512, 40
+    r = np.arange(1, n + 1, dtype=np.float64)
+    mag = np.where(r <= 20, 10 * r, np.where(r <= 255, 200 + (r - 20), 435 + 300 * (r - 255)))
+    H = codes.rlc_H(n, n - m, seed=7)
+    if both:
+        H[:, 53] = H[:, 0] ^ H[:, 1] ^ H[:, 254] ^ H[:, 2] ^ H[:, 20]
+    sets = [(1, 2, 255), (3, 21, 54), (255,), (1, 255), (21, 255), (256,), (2, 256)]
+    llr = np.tile(-mag, (len(sets), 1)).astype(np.float32)
+    for i, s in enumerate(sets):
+        llr[i, np.array(s) - 1] *= -1
+    want = _mline(gpu_device, H, llr, 10 ** 5, 3, f"rank 255 both={both}")
+    assert (want[3] == 3).all() and (want[2][:2] == 0).all()
+
+
+def test_mline_rank_255_two_lines(gpu_device):
+    """As above with two lines: ranks 255 and 382 weigh the same."""
+    print("mline rank 255 two lines", flush=True)
+    n, m = 512, 40
+    r = np.arange(1, n + 1, dtype=np.float64)
+    mag = np.where(r <= 255, 1000 + 1.5 * r, 1000 + 1.5 * 255 + (r - 255))
+    H = codes.rlc_H(n, n - m, seed=8)
+    sets = [(254,), (255,), (256,), (257,), (381,), (382,), (383,), (1, 2)]
+    llr = np.tile(-mag, (len(sets), 1)).astype(np.float32)
+    for i, s in enumerate(sets):
+        llr[i, np.array(s) - 1] *= -1
+    want = _mline(gpu_device, H, llr, 5000, 2, "rank 255 two lines")
+    assert (want[2][:7] == 0).all()
+
+
+@pytest.mark.parametrize("segments,weak", [(2, 255), (3, 255), (4, 255), (4, 254), (3, 256)])
+def test_mline_weak_and_strong_halves(gpu_device, segments, weak):
+    """n = 512 with as many weak positions as put an anchor at or beside rank 255;
+    words a few flips from a codeword."""
+    print(f"mline halves segments={segments} weak={weak}", flush=True)
+    n, m, N = 512, 24, 48
+    rng = np.random.default_rng(segments * 1000 + weak)
+    H = codes.rlc_H(n, n - m, seed=9)
+    cw = channel.encode(codes.generator_matrix(H), rng.integers(0, 2, size=(N, n - m), dtype=np.uint8))
+    llr = np.empty((N, n), dtype=np.float32)
+    for b in range(N):
+        mag = np.sort(np.concatenate([rng.uniform(0.3, 1.0 + 0.2 * (b % 4), weak), rng.uniform(1.5 + 2 * (b % 3), 9.0, n - weak)]))
+        perm = rng.permutation(n)
+        rx = cw[b].copy()
+        rx[perm[rng.choice(262, size=1 + b % 3, replace=False)]] ^= 1
+        if b % 2:
+            rx[perm[254]] ^= 1
+        llr[b, perm] = mag * (2.0 * rx[perm] - 1)
+    _mline(gpu_device, H, llr, 30000, segments, f"halves {segments} {weak}", jdiv=bool(weak & 1) and segments == 4)
