@@ -155,23 +155,37 @@ hipError_t launch_walk(const MlineArgs& a, int grid, hipStream_t stream)
 
 }  // namespace
 
-// The match search decodes nearly every block; mline_kernel the ones it marks.
+// Small batches (up to ORBG_ML_SMALL blocks, n <= 256) go through the searches and the
+// walk in one launch: 64 blocks of n = 127, two lines, 21.2 us, 23.6 as two launches;
+// 500 blocks of n = 256, three lines, 28.0 / 28.9; but 2000 blocks of n = 64, one line,
+// 26.0 / 22.4 and 16 blocks of n = 512, two lines, 63.7 / 54.5 (its registers are cut
+// harder).  Else the narrow search decodes nearly every block and mline_kernel those
+// that it marks: in spans of one flag up to ORBG_ML_SPANS blocks, so that no wave is
+// left with many of them, longer ones above (more waves that only read their flags
+// cost more than they save).  64 blocks of n = 512 that no search covers, two lines,
+// 20000 queries: 11.9 ms, 496 in one span of 64.
+#define ORBG_ML_SMALL 1024
+#define ORBG_ML_SPANS 8192
 hipError_t launch_mline(const MlineArgs& a, int grid, hipStream_t stream)
 {
     if (a.nblocks <= 0) return hipSuccess;
     MlineArgs w = a;
-    w.marked = get_sets(a.n, stream, &w.sets);
-    if (w.marked) {
-        hipError_t e;
-        if (a.n <= ORBG_WAVE) e = launch_mline_match_nk<1>(w, grid, stream);
-        else if (a.n <= 2 * ORBG_WAVE) e = launch_mline_match_nk<2>(w, grid, stream);
-        else if (a.n <= 4 * ORBG_WAVE) e = launch_mline_match_nk<4>(w, grid, stream);
-        else e = launch_mline_match_nk<8>(w, grid, stream);
-        if (e != hipSuccess) return e;
-        const int64_t spans = (a.nblocks + ORBG_WAVE - 1) / ORBG_WAVE;   // abandon flags are read 64 at a time
-        grid = (int)(spans < grid / 4 ? spans : grid / 4 > 0 ? grid / 4 : 1);
+    w.span = 0;
+    if (!get_sets(a.n, stream, &w.sets)) return launch_walk(w, grid, stream);
+    if (a.nblocks <= ORBG_ML_SMALL && a.n <= 4 * ORBG_WAVE) {
+        if (a.n <= ORBG_WAVE) return launch_mline_all_nk<1>(w, (int)a.nblocks, stream);
+        if (a.n <= 2 * ORBG_WAVE) return launch_mline_all_nk<2>(w, (int)a.nblocks, stream);
+        return launch_mline_all_nk<4>(w, (int)a.nblocks, stream);
     }
-    return launch_walk(w, grid, stream);
+    w.span = 1;
+    while (w.span < ORBG_WAVE && a.nblocks > (int64_t)ORBG_ML_SPANS * w.span) w.span *= 2;
+    const int64_t spans = (a.nblocks + w.span - 1) / w.span;
+    hipError_t e;
+    if (a.n <= ORBG_WAVE) e = launch_mline_match_nk<1>(w, grid, stream);
+    else if (a.n <= 2 * ORBG_WAVE) e = launch_mline_match_nk<2>(w, grid, stream);
+    else if (a.n <= 4 * ORBG_WAVE) e = launch_mline_match_nk<4>(w, grid, stream);
+    else e = launch_mline_match_nk<8>(w, grid, stream);
+    return e != hipSuccess ? e : launch_walk(w, (int)(spans < grid ? spans : grid), stream);
 }
 
 }  // namespace orbg

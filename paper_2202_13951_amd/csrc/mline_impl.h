@@ -1034,18 +1034,26 @@ __device__ __forceinline__ void decode_walk(const Model& md, const uint32_t* tbl
     nwin = c.nwin;
 }
 
-// Five waves per SIMD for one or two keys per lane (the walk is latency-bound:
-// measured 4% faster than the four the register count gives by itself, at a
-// 20-byte spill for two keys); four keys keep the compiler's choice.  MM: the
-// largest number of segments the launch's fits may use (a.mseg); only the
-// walks up to MM are compiled into the kernel, which keeps the registers of a
-// two-line decode free of the three- and four-line walks' state.
-template <int NK, int MM>
-__global__ void __launch_bounds__(ORBG_WAVE) __attribute__((amdgpu_waves_per_eu(NK <= 2 ? 5 : 1))) mline_kernel(MlineArgs a)
+// One wave per block.  The blocks that the narrow search left marked (a.span) go
+// through the wide search and, where that does not cover them either, the walk of the
+// order; ALL: a small batch in one launch, each block through the narrow search too
+// (64 blocks: 21 us, 24 as two launches).  Without the lists (a.span = 0, not ALL)
+// every block is walked.
+// The walk is latency-bound, so the searches inlined before it must not take its
+// waves: the registers are cut for as many as it has alone (its LDS allows four for
+// one or two keys per lane).  MM: the largest number of segments the launch's fits
+// may use (a.mseg); only the walks up to MM are compiled into the kernel, which keeps
+// the registers of a two-line decode free of the three- and four-line walks' state.
+template <int NK, int MM, bool ALL>
+__global__ void __launch_bounds__(ORBG_WAVE, NK <= 2 ? 4 : 3) mline_kernel(MlineArgs a)
 {
+    BlockCursor cur(a.span > 0 ? a.abandoned : nullptr, a.nblocks, a.span);
+    int64_t b = cur.next();
+    if (b < 0) return;
     __shared__ union {
         MlLds<NK * ORBG_WAVE> walk;
-        MmLds<NK, uint64_t, true> match;
+        MmLds<ALL ? NK : 1, uint64_t, false> narrow;
+        MmLds<NK, uint64_t, true> wide;
     } lds;
     auto& S = lds.walk;
     const int lane = lane_id();
@@ -1054,8 +1062,7 @@ __global__ void __launch_bounds__(ORBG_WAVE) __attribute__((amdgpu_waves_per_eu(
     uint64_t hrow[NK];
 #pragma unroll
     for (int j = 0; j < NK; ++j) hrow[j] = lane < a.m ? a.rows[lane * NK + j] : 0ull;
-    BlockCursor cur(a.marked ? a.abandoned : nullptr, a.nblocks, ORBG_WAVE);
-    for (int64_t b = cur.next(); b >= 0; b = cur.next()) {
+    for (; b >= 0; b = cur.next()) {
         const float* row = a.llr + b * (int64_t)n;
         float x[NK];
         bool ybit[NK];
@@ -1068,8 +1075,10 @@ __global__ void __launch_bounds__(ORBG_WAVE) __attribute__((amdgpu_waves_per_eu(
             const uint64_t y = ballot(ybit[j]);
             acc += __popcll(hrow[j] & y);
         }
-        // a block that the first search left for its large weights
-        if (a.marked && mline_match_block<NK, uint64_t, true>(a, a.sets, lds.match, x, hrow, b) != 0) continue;
+        if constexpr (ALL) {
+            if (mline_match_block<NK, uint64_t, false>(a, a.sets, lds.narrow, x, hrow, b) != 0) continue;
+        }
+        if ((ALL || a.span > 0) && mline_match_block<NK, uint64_t, true>(a, a.sets, lds.wide, x, hrow, b) != 0) continue;
         const uint64_t s0 = uniform_u64(ballot((acc & 1u) != 0u));
         bool found = false;
         uint32_t q = a.budget;
@@ -1152,10 +1161,17 @@ __global__ void __launch_bounds__(ORBG_WAVE) __attribute__((amdgpu_waves_per_eu(
 template <int MM>
 hipError_t launch_mline_m(const MlineArgs& a, int grid, hipStream_t stream)
 {
-    if (a.n <= ORBG_WAVE) mline_kernel<1, MM><<<grid, ORBG_WAVE, 0, stream>>>(a);
-    else if (a.n <= 2 * ORBG_WAVE) mline_kernel<2, MM><<<grid, ORBG_WAVE, 0, stream>>>(a);
-    else if (a.n <= 4 * ORBG_WAVE) mline_kernel<4, MM><<<grid, ORBG_WAVE, 0, stream>>>(a);
-    else mline_kernel<8, MM><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    if (a.n <= ORBG_WAVE) mline_kernel<1, MM, false><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    else if (a.n <= 2 * ORBG_WAVE) mline_kernel<2, MM, false><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    else if (a.n <= 4 * ORBG_WAVE) mline_kernel<4, MM, false><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    else mline_kernel<8, MM, false><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    return hipGetLastError();
+}
+
+template <int NK>
+hipError_t launch_mline_all_nk(const MlineArgs& a, int grid, hipStream_t stream)
+{
+    mline_kernel<NK, ORBG_ML_MSEG, true><<<grid, ORBG_WAVE, 0, stream>>>(a);
     return hipGetLastError();
 }
 

@@ -254,7 +254,8 @@ struct MmSearch {
     // of such a set of c weighs at most w - (c - 1) lone; over the ranks that do,
     // v_r >= (a r + g) / k (a: the slope from the lowest of them to the highest,
     // though any positive value is valid; g exact for it), so the set's rank sum
-    // is at most (k w - c g) / a.
+    // is at most (k w - c g) / a, and that of the c highest such ranks (on a nearly
+    // flat stretch a is small and the first bound says little).
     __device__ __forceinline__ bool prefixes(uint32_t w, uint32_t& end) const
     {
         const uint32_t lane = (uint32_t)lane_id();
@@ -291,7 +292,9 @@ struct MmSearch {
             const int g = (int)(wave_min_u32((uint32_t)gm ^ 0x80000000u) ^ 0x80000000u);
             const int num = k * (int)w - (int)c * g;
             const float fs = (float)num * __builtin_amdgcn_rcpf((float)a) * 1.00001f + 0.01f;
-            const int sum = num < 0 ? 0 : (int)uniform_u32((uint32_t)(fs < 1e6f ? (int)fs : 1000000));
+            const int line = num < 0 ? 0 : (int)uniform_u32((uint32_t)(fs < 1e6f ? (int)fs : 1000000));
+            const int tops = (int)(c * rhi) - (int)(c * (c - 1) / 2);   // (below 9 c and more: no such set)
+            const int sum = line < tops ? line : tops < 0 ? 0 : tops;
             if (c > ORBG_HIGH_SLOTS) return sum < 100;    // 9 + ... + 16: a set of eight
             if (sum > T.limit[c]) return false;
             const uint32_t e = T.end[c * ORBG_MM_SUMS + (uint32_t)(sum < ORBG_MM_SUMS ? sum : ORBG_MM_SUMS - 1)];
@@ -482,11 +485,16 @@ struct MmSearch {
         MmSplit po = {0u, 0u, 0u, 0u};
         if (with) po = split_of(o.mask, o.x, o.y);
         uint32_t total = 0;                               // per lane: at most 256 per set
+        const uint32_t second = WIDE ? uniform_u32(L.hist[1] >> 8) : 0u;
         auto add = [&](uint32_t x, uint32_t y, uint32_t wu, auto&& split) {
             const bool some = wu <= w;
             const uint32_t left = some ? w - wu : 0u;
-            const uint32_t upto = subsets_upto(left);
-            const uint32_t under = left != 0 ? subsets_upto(left - 1u) : 0u;
+            uint32_t upto = 1u, under = left != 0 ? 1u : 0u;
+            // (wide: most steps leave room for the empty subset alone)
+            if (!WIDE || ballot(left >= second) != 0ull) {
+                upto = subsets_upto(left);
+                under = left != 0 ? subsets_upto(left - 1u) : 0u;
+            }
             uint32_t n = some ? under : 0u;
             if (with) {
                 MmSplit p = {0u, 0u, 0u, 0u};

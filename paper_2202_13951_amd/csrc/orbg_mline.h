@@ -44,7 +44,8 @@ struct MlineArgs {
     int32_t* mfit;             // per-block segment count, or nullptr
     int32_t* j0;               // per-block J_0 of the fit (the 1-line offset for one segment), or nullptr
     MlineSets sets;            // match search
-    bool marked;               // only the blocks that the match search left (marked in abandoned)
+    int span;                  // mline_kernel: 0: every block; else those that the search before left
+                               // (marked in abandoned), each wave taking spans of this many (<= 64) flags
 };
 
 // Entries of the subset-count table: (LMAX + 1) x (WMAX + 1) x SMAX.
@@ -58,6 +59,11 @@ extern template hipError_t launch_mline_match_nk<1>(const MlineArgs&, int, hipSt
 extern template hipError_t launch_mline_match_nk<2>(const MlineArgs&, int, hipStream_t);
 extern template hipError_t launch_mline_match_nk<4>(const MlineArgs&, int, hipStream_t);
 extern template hipError_t launch_mline_match_nk<8>(const MlineArgs&, int, hipStream_t);
+template <int NK>
+hipError_t launch_mline_all_nk(const MlineArgs& a, int grid, hipStream_t stream);
+extern template hipError_t launch_mline_all_nk<1>(const MlineArgs&, int, hipStream_t);
+extern template hipError_t launch_mline_all_nk<2>(const MlineArgs&, int, hipStream_t);
+extern template hipError_t launch_mline_all_nk<4>(const MlineArgs&, int, hipStream_t);
 // The kernels for fits of at most MM segments (one translation unit each).
 template <int MM>
 hipError_t launch_mline_m(const MlineArgs& a, int grid, hipStream_t stream);

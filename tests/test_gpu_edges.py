@@ -109,3 +109,40 @@ def test_mline_weak_and_strong_halves(gpu_device, segments, weak):
             rx[perm[254]] ^= 1
         llr[b, perm] = mag * (2.0 * rx[perm] - 1)
     _mline(gpu_device, H, llr, 30000, segments, f"halves {segments} {weak}", jdiv=bool(weak & 1) and segments == 4)
+
+
+@pytest.mark.parametrize("n,m,segments", [(256, 24, 1), (512, 22, 2)])
+def test_mline_blocks_that_no_search_covers_run_side_by_side(gpu_device, n, m, segments):
+    """Large offsets: the pairs that reach past rank 254 come before the budget's
+    end, so every block is left to the walk of the order.  Each has a wave of its
+    own: 64 blocks take about as long as the slowest alone (as long as all of them
+    one after the other where one wave decoded them); results as the oracle's."""
+    print(f"mline side by side n={n}", flush=True)
+    budget, N = 20000, 64
+    rng = np.random.default_rng(5)
+    H = codes.rlc_H(n, n - m, seed=n)
+    mag = np.sort(10 + 0.01 * np.arange(n) + 0.01 * rng.standard_normal((N, n)), axis=1)
+    llr = np.empty((N, n), dtype=np.float32)
+    for b in range(N):
+        perm = rng.permutation(n)
+        llr[b, perm] = mag[b] * (2.0 * rng.integers(0, 2, n) - 1)
+    x = torch.from_numpy(llr).to(gpu_device)
+    got = binding.orbg_decode_mline(H, x[:16].contiguous(), budget, segments)[:3]
+    _check(got, O.decode_mline(H, llr[:16], budget, segments, threads=THREADS)[:3], f"side by side n={n}")
+
+    def best_of(rows, reps):
+        best = float("inf")
+        for _ in range(reps):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            binding.orbg_decode_mline(H, rows, budget, segments)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    alone = [best_of(x[i:i + 1], 3) for i in range(N)]
+    for rows, reps in ((x, 3), (x.repeat(20, 1), 2)):    # both sides of the one-launch batch size
+        t = best_of(rows, reps)
+        limit = 3 * max(alone) + rows.shape[0] / 1024 * sum(alone) / N
+        assert t <= limit, f"{rows.shape[0]} blocks {t:.2f} ms; alone {max(alone):.2f} at most, {sum(alone):.2f} in all"
