@@ -3,6 +3,7 @@
 // kernel compiled for the request's largest segment count (mline_impl.h).
 #include <map>
 #include <mutex>
+#include <new>
 #include <utility>
 #include <vector>
 
@@ -134,11 +135,15 @@ bool get_sets(int n, hipStream_t stream, MlineSets* out)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
     MlineSets t = {};
-    if (make_sets(top, &t) != hipSuccess) {
-        (void)hipGetLastError();
+    try {
+        if (make_sets(top, &t) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        sets_of[{dev, top}] = t;
+    } catch (const std::bad_alloc&) {
         return false;
     }
-    sets_of[{dev, top}] = t;
     *out = t;
     return true;
 }

@@ -55,7 +55,7 @@ struct Schedule {
     int rmax;           // largest rank any entry references
     int rmax0;          // largest rank an entry of the first batch of 64 references
     int wlast;          // logistic weight of the last entry
-    MatchTable match;   // empty for n <= 8
+    MatchTable match;   // empty for n <= 8, or where there is no memory for it
 };
 
 // 1-line ORBGRAND schedules for one (n, len): j0max + 2 schedules of `len`
@@ -72,8 +72,9 @@ struct Schedule1 {
 };
 
 int orbg_build_schedule(int n, uint64_t len, hipStream_t stream, Schedule* out, char* err, size_t errlen);
-// Match-search tables for patterns of logistic weight <= wlast (<= 100).
-int orbg_build_match(int n, int wlast, MatchTable* out, char* err, size_t errlen);
+// Match-search tables for patterns of logistic weight <= wlast (<= 100); left empty
+// where device memory cannot hold them.
+void orbg_build_match(int n, int wlast, MatchTable* out);
 int orbg_build_schedule_1line(int n, uint64_t len, hipStream_t stream, Schedule1* out, char* err, size_t errlen);
 // Unpacks `count` entries from `entries` to 16-byte lists of 1-based ranks.
 int orbg_unpack_entries(const uint2* entries, uint64_t count, uint8_t* d_out, hipStream_t stream);

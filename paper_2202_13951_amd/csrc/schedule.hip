@@ -31,6 +31,7 @@
 #include "orbg_internal.h"
 
 #include <algorithm>
+#include <new>
 #include <stdint.h>
 #include <vector>
 
@@ -257,14 +258,19 @@ int orbg_build_schedule(int n, uint64_t len, hipStream_t stream, Schedule* out, 
     out->rmax = rmax[0];
     out->rmax0 = rmax[1];
     out->wlast = host_small[1];
-    const int rc = n > ORBG_LOW_RANKS ? orbg_build_match(n, out->wlast, &out->match, err, errlen) : 0;
-    if (rc != 0) (void)hipFree(d_entries);
-    return rc;
+    if (n > ORBG_LOW_RANKS) {
+        // (without them decodes go by steps of the order)
+        try {
+            orbg_build_match(n, out->wlast, &out->match);
+        } catch (const std::bad_alloc&) {
+        }
+    }
+    return 0;
 }
 
 // Every set is listed by a depth-first walk on the host (80 thousand sets for
 // the largest limit), sorted by a counting sort over (weight, size).
-int orbg_build_match(int n, int wlast, MatchTable* out, char* err, size_t errlen)
+void orbg_build_match(int n, int wlast, MatchTable* out)
 {
     const int WC = ORBG_MATCH_WCOL, RW = ORBG_WMAX_H + 1, top = n < ORBG_WLEVEL_SCHED ? n : ORBG_WLEVEL_SCHED;
     const uint32_t cap = 1u << 24;                    // counts saturate above every budget
@@ -323,15 +329,13 @@ int orbg_build_match(int n, int wlast, MatchTable* out, char* err, size_t errlen
                hipMemcpy(*d, h.data(), h.size() * sizeof(h[0]), hipMemcpyHostToDevice) == hipSuccess;
     };
     if (!put(&out->sets, sets) || !put(&out->below, below) || !put(&out->above, above)) {
-        snprintf(err, errlen, "schedule: cannot place the match-search tables (%zu sets)", keys.size());
         (void)hipFree(out->sets);
         (void)hipFree(out->below);
         (void)hipFree(out->above);
+        (void)hipGetLastError();
         out->sets = nullptr;
         out->below = out->above = nullptr;
-        return -2;
     }
-    return 0;
 }
 
 int orbg_unpack_schedule(const Schedule* s, uint64_t count, uint8_t* d_out, hipStream_t stream)
