@@ -33,6 +33,12 @@
 
 namespace orbg {
 
+// Check bits up to which a match's combinations of null masks (2^(8 - m) at least) are
+// spread over the lanes.  In every kernel this costs the searches of other codes 2 to
+// 4 % (scalar spills).  100 blocks of n = 128, us, one by one / by lanes / the walk of
+// the order: m = 1 37.8 / 16.4 / 21.2, m = 2 22.0 / 16.4 / 21.2; from m = 4 on one by
+// one is no slower.
+#define ORBG_MATCH_FEW 3
 #define ORBG_MATCH_SOME 44       // fewest ranks of a partial ranking (at most 63), where the limit needs as many
 
 template <typename S>
@@ -53,6 +59,27 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
     return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
            __builtin_amdgcn_readlane(v, 48);
 }
+
+// Largest and smallest u32 of the wave, wave-uniform (all lanes active).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
+{
+#define ORBG_MAX_STEP(ctrl)                                                              \
+    {                                                                                    \
+        const uint32_t o = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xF, 0xF, false); \
+        v = o > v ? o : v;                                                               \
+    }
+    ORBG_MAX_STEP(0xB1)      // quad_perm [1,0,3,2]
+    ORBG_MAX_STEP(0x4E)      // quad_perm [2,3,0,1]
+    ORBG_MAX_STEP(0x141)     // row_half_mirror
+    ORBG_MAX_STEP(0x140)     // row_mirror
+#undef ORBG_MAX_STEP
+    const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+    const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+    const uint32_t e = a > b ? a : b, f = c > d ? c : d;
+    return e > f ? e : f;
+}
+
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) { return ~wave_max_u32(~v); }
 
 // A pattern by its place in the order: key = (logistic weight << 16) | (Hamming
 // weight << 8) | (255 - mask of ranks 1..8 with its bits reversed), then the
@@ -232,7 +259,10 @@ __device__ __forceinline__ S match_reduce(S (&g)[NC], uint32_t* null, uint32_t& 
 // reach): reach = the ranks whose columns are in L.h (every set of a weight up
 // to it holds only those).  visit(pattern) is called for each match whose
 // weight is at most limit().  Returns the step to go on from with more ranks.
-template <typename S, typename Limit, typename Visit>
+// FEW (codes of at most ORBG_MATCH_FEW check bits, whose first eight columns have many
+// null combinations): for the earliest match of each set only, which is enough where
+// the earliest of all is looked for.
+template <bool FEW, typename S, typename Limit, typename Visit>
 __device__ __forceinline__ uint32_t match_scan(const uint2* __restrict__ sets, const MatchLds<S>& L, S sv, S piv,
                                                uint32_t nulls, uint32_t t, uint32_t reach, Limit&& limit,
                                                Visit&& visit)
@@ -255,10 +285,36 @@ __device__ __forceinline__ uint32_t match_scan(const uint2* __restrict__ sets, c
         if (ballot(match) != 0ull) {
             uint32_t m = (uint32_t)v & 0xffu;
             const uint32_t size = set_size(e0.x, e0.y);
+            auto key_of = [&](uint32_t w, uint32_t sz, uint32_t mk) -> uint32_t {
+                return ((w + mask_weight(mk)) << 16) | ((sz + __popc(mk)) << 8) | (255u - (__builtin_bitreverse32(mk) >> 24));
+            };
+            if constexpr (FEW) {
+                // one match after the other, its combinations of the null masks one per
+                // lane
+                for (uint64_t left = ballot(match && wu <= limit()); left != 0;) {
+                    const int l = __builtin_ctzll(left);
+                    const uint32_t ml = (uint32_t)__builtin_amdgcn_readlane((int)m, l);
+                    const uint32_t wl = (uint32_t)__builtin_amdgcn_readlane((int)wu, l);
+                    const uint32_t sl = (uint32_t)__builtin_amdgcn_readlane((int)size, l);
+                    uint32_t least = ~0u;
+                    for (uint32_t k = (uint32_t)lane; k < (1u << nulls); k += ORBG_WAVE) {
+                        uint32_t mk = ml;
+                        for (uint32_t i = 0; i < nulls; ++i) mk ^= ((k >> i) & 1u) != 0 ? L.null[i] : 0u;
+                        const uint32_t key = key_of(wl, sl, mk);
+                        least = key < least ? key : least;
+                    }
+                    Pattern p;
+                    p.key = wave_min_u32(least);
+                    p.x = (uint32_t)__builtin_amdgcn_readlane((int)e0.x, l);
+                    p.y = (uint32_t)__builtin_amdgcn_readlane((int)e0.y, l);
+                    if (pattern_weight(p) <= limit()) visit(p);
+                    left &= left - 1;
+                    left &= ballot(wu <= limit());
+                }
+            }
             // every combination of the null masks (one after the other by Gray code)
-            for (uint32_t k = 0;;) {
-                const uint32_t key = ((wu + mask_weight(m)) << 16) | ((size + __popc(m)) << 8) |
-                                     (255u - (__builtin_bitreverse32(m) >> 24));
+            for (uint32_t k = 0; !FEW;) {
+                const uint32_t key = key_of(wu, size, m);
                 for (uint64_t left = ballot(match && (key >> 16) <= limit()); left != 0;) {
                     const int l = __builtin_ctzll(left);
                     Pattern p;
@@ -281,7 +337,7 @@ __device__ __forceinline__ uint32_t match_scan(const uint2* __restrict__ sets, c
 }
 
 // One block: its first member within the budget, written to its outputs.
-template <int NK, bool ORDERED, typename S, class CD, class LO>
+template <int NK, bool ORDERED, bool FEW, typename S, class CD, class LO>
 __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t (&hrow)[NK], const CD& c,
                                             const S* __restrict__ cols, MatchLds<S>& L, uint32_t budget,
                                             uint32_t ordv, buf_t cw_row, uint64_t* q_out, uint8_t* ab_out,
@@ -296,6 +352,8 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
     const uint32_t lim = min(budget, c.slen);
     uint32_t q = 0;                                       // 0: not found
     Pattern best = {~0u, ~0u, ~0u};
+    uint32_t empty = 1u;                                  // query 1 is the empty pattern, but not always where a
+                                                          // batch order found it
     if (s0 == 0 && (!ORDERED || (uint32_t)__builtin_amdgcn_readfirstlane((int)ordv) == 0u)) {
         q = 1;
     } else {
@@ -374,13 +432,14 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
                 wave_lds_sync();
                 reach = ALL;
             }
-            t = match_scan<S>(c.sets, L, sv, piv, nulls, t, reach, limit, visit);
+            t = match_scan<FEW>(c.sets, L, sv, piv, nulls, t, reach, limit, visit);
             if (reach < limit()) {                        // more ranks are needed
                 reach = 0;
                 continue;
             }
             if (ORDERED && phase == 0) {
                 q = at + 1u;                              // 0: no match
+                empty = 0u;
                 if (q != 0 || lim <= PREFIX) break;
                 phase = 1;
                 best = none;
@@ -393,9 +452,7 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
         if (q > lim) q = 0;
     }
     uint32_t win_lo = 0, win_hi = 0;
-    // a pattern was found (a batch order can make any pattern query 1, not only the
-    // empty one): as a schedule entry, byte 0 the mask, then the ranks
-    if (q != 0 && best.x != ~0u) {
+    if (q > empty) {                                      // as a schedule entry: byte 0 the mask, then the ranks
         win_lo = pattern_mask(best) | ((best.x >> 16) & 0xff00u) | (best.x & 0xff0000u) | (best.x << 16 & 0xff000000u);
         win_hi = (best.x & 0xffu) | ((best.y >> 16) & 0xff00u) | (best.y & 0xff0000u) | (best.y << 16 & 0xff000000u);
     }
@@ -464,7 +521,7 @@ constexpr int match_waves()
 // ids[i]; ORDERED: with the batch order of row i.  Every lookup uses NK keys
 // per lane (the largest of the launch's codes; keys past a code's length are
 // ranked last).
-template <int NK, bool ORDERED, typename S, bool MIXED>
+template <int NK, bool ORDERED, typename S, bool MIXED, bool FEW>
 __global__ void __launch_bounds__(ORBG_WAVE, (match_waves<NK, ORDERED, S>()))
 match_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int64_t* __restrict__ row_off,
              const float* __restrict__ llr, int64_t nblocks, uint32_t budget, const uint8_t* __restrict__ order,
@@ -535,7 +592,7 @@ match_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
         } else {
             load_hrows_pad<NK>(s_rows + c.row_base, c.m, c.nk, hr);
         }
-        match_block<NK, ORDERED, S>(cur_in.x, hr, c, s_cols + c.col_base, L, budget, cur_in.ordv,
+        match_block<NK, ORDERED, FEW, S>(cur_in.x, hr, c, s_cols + c.col_base, L, budget, cur_in.ordv,
                                     make_buf(cw + (cur_in.row >= 0 ? cur_in.row : 0), cur_in.row >= 0 ? (uint32_t)c.n : 0u),
                                     queries + cur_in.oid, abandoned + cur_in.oid, guess, NoOffs{});
         if (b < 0) break;
@@ -543,7 +600,7 @@ match_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
     }
 }
 
-template <int NK, bool ORDERED, typename S, bool MIXED>
+template <int NK, bool ORDERED, typename S, bool MIXED, bool FEW = false>
 static hipError_t launch_match_as(const DecodeArgs& a, bool marked, hipStream_t stream)
 {
     uint32_t ncols = 0;
@@ -561,7 +618,7 @@ static hipError_t launch_match_as(const DecodeArgs& a, bool marked, hipStream_t 
     }
     const int64_t units = marked ? (a.nblocks + span - 1) / span : a.nblocks;
     const int64_t grid = units < most ? units : most;
-    match_kernel<NK, ORDERED, S, MIXED><<<(unsigned)grid, ORBG_WAVE, lds, stream>>>(
+    match_kernel<NK, ORDERED, S, MIXED, FEW><<<(unsigned)grid, ORBG_WAVE, lds, stream>>>(
         a.codes, a.block_code, a.row_off, a.llr, a.nblocks, a.budget, a.order, a.cw, a.queries, a.abandoned, span,
         a.ids, a.row_limit);
     return hipGetLastError();
@@ -579,6 +636,7 @@ hipError_t launch_match_nk(const DecodeArgs& a, bool s32, bool marked, hipStream
     if (a.order)
         return s32 ? launch_match_as<NK, true, uint32_t, false>(a, marked, stream)
                    : launch_match_as<NK, true, uint64_t, false>(a, marked, stream);
+    if (a.codes.c[0].m <= ORBG_MATCH_FEW) return launch_match_as<NK, false, uint32_t, false, true>(a, marked, stream);
     return s32 ? launch_match_as<NK, false, uint32_t, false>(a, marked, stream)
                : launch_match_as<NK, false, uint64_t, false>(a, marked, stream);
 }

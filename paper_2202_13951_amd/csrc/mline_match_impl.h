@@ -91,26 +91,6 @@ struct MmLds {
     uint8_t sub[256];                   // narrow: the subsets by ascending weight
 };
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
-{
-#define ORBG_MAX_STEP(ctrl)                                                              \
-    {                                                                                    \
-        const uint32_t o = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xF, 0xF, false); \
-        v = o > v ? o : v;                                                               \
-    }
-    ORBG_MAX_STEP(0xB1)      // quad_perm [1,0,3,2]
-    ORBG_MAX_STEP(0x4E)      // quad_perm [2,3,0,1]
-    ORBG_MAX_STEP(0x141)     // row_half_mirror
-    ORBG_MAX_STEP(0x140)     // row_mirror
-#undef ORBG_MAX_STEP
-    const uint32_t a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
-    const uint32_t c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
-    const uint32_t e = a > b ? a : b, f = c > d ? c : d;
-    return e > f ? e : f;
-}
-
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) { return ~wave_max_u32(~v); }
-
 // The fitted model (wave-uniform): m segments, segment i of ranks I[i] + 1 ..
 // I[i + 1], offsets J[i], slopes B[i].
 struct MmModel {

@@ -1,6 +1,6 @@
 """GPU parity with the CPU oracle, bit for bit, at edges of the match searches and
 of the passes in front of them: results at the first position of a batch order,
-ranks past those that the m-line search's sets hold."""
+codes of few check bits, ranks past those that the m-line search's sets hold."""
 import os
 
 import numpy as np
@@ -13,6 +13,7 @@ from synth import channel, codes
 
 pytestmark = pytest.mark.gpu
 THREADS = min(16, os.cpu_count() or 1)
+DIRECT = 24576                       # largest batch decoded by one launch
 
 
 def _check(got, want, tag):
@@ -45,6 +46,49 @@ def test_first_query_of_a_batch_order(gpu_device, n, m, budget):
     want = O.decode_ordered(H, llr, budget, order, THREADS)
     assert (want[1] == 1).all() and (want[0] == cw).all()
     _check(got, want, f"order n={n} budget={budget}")
+
+
+@pytest.mark.parametrize("n", [9, 30, 64, 100, 129, 300, 700])
+@pytest.mark.parametrize("m", [1, 2, 3, 4])
+def test_few_check_bits(gpu_device, n, m):
+    """The first eight columns of a code of m check bits have at least 2^(8 - m) null
+    combinations; magnitudes on a coarse grid in a third of the blocks, zero columns
+    in the matrix; both sides of the one-launch batch size."""
+    print(f"few check bits n={n} m={m}", flush=True)
+    rng = np.random.default_rng(n * 10 + m)
+    H = rng.integers(0, 2, size=(m, n), dtype=np.uint8)
+    H[:, :m] = np.eye(m, dtype=np.uint8)
+    H[:, n // 2:n // 2 + 3] = 0
+    for blocks in (300, DIRECT + 5):
+        llr = (rng.standard_normal((blocks, n)) * 3).astype(np.float32)
+        llr[::3] = np.round(llr[::3])
+        got = binding.orbg_decode(H, torch.from_numpy(llr).to(gpu_device), min(500, 2 ** n))
+        _check(got, O.decode(H, llr, min(500, 2 ** n), THREADS), f"few n={n} m={m} blocks={blocks}")
+
+
+def test_few_check_bits_cost_no_more_than_many(gpu_device):
+    """One check bit: 128 null combinations beside every match.  500 blocks, n = 128:
+    16.5 us, 17 with eight check bits (38 with the combinations one after the other)."""
+    print("few check bits, time", flush=True)
+    n, blocks = 128, 500
+    x = torch.from_numpy((np.random.default_rng(3).standard_normal((blocks, n)) * 3).astype(np.float32)).to(gpu_device)
+
+    def time_of(m):
+        H = codes.rlc_H(n, n - m, seed=n)
+        out = binding.orbg_decode(H, x, 1000)
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(40):
+                binding.orbg_decode(H, x, 1000, out=out)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    one, eight = time_of(1), time_of(8)
+    assert one <= 1.6 * eight, f"m = 1: {one / 40 * 1e3:.1f} us, m = 8: {eight / 40 * 1e3:.1f} us"
 
 
 def _mline(dev, H, llr, budget, segments, tag, jdiv=False):
