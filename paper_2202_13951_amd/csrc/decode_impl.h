@@ -228,6 +228,18 @@ __device__ __forceinline__ S hard_decision(const float (&x)[NK], int n, const ui
 template <int NK>
 struct IndexBits { static constexpr int value = NK == 1 ? 6 : NK == 2 ? 7 : NK == 4 ? 8 : NK == 8 ? 9 : 10; };
 
+// No element has a bit that the 32-bit keys drop (values on a coarse grid, as
+// quantised LLRs are): equal truncated magnitudes are equal magnitudes, which rank by
+// index, as the keys do.
+template <int NK>
+__device__ __forceinline__ bool coarse_row(const float (&x)[NK])
+{
+    uint32_t any = 0;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) any |= __float_as_uint(x[j]);
+    return ballot((any & ((1u << (IndexBits<NK>::value - 1)) - 1u)) != 0u) == 0ull;
+}
+
 // Step 3a: received index of every rank, idx[j] for rank lane * NK + j + 1.
 // The sort runs on 32-bit keys (top bits of |LLR| above the index); that order
 // is the order of the full keys (bits of |LLR|) << 32 | index except inside runs
@@ -235,8 +247,8 @@ struct IndexBits { static constexpr int value = NK == 1 ? 6 : NK == 2 ? 7 : NK =
 // schedule reaches share a truncated magnitude, the full 64-bit keys are
 // sorted instead; hfit > 0 adds ranks 1 and hfit to the ranks whose element
 // must be exact (their magnitudes fit the 1-line model).  Positions past n hold
-// keys above every element.
-template <int NK>
+// keys above every element.  COARSE: rows on a coarse grid need no full keys.
+template <int NK, bool COARSE = false>
 __device__ __forceinline__ void rank_order(const float (&x)[NK], int n, int rdepth, int hfit, uint32_t (&idx)[NK])
 {
     constexpr int IB = IndexBits<NK>::value;
@@ -259,7 +271,7 @@ __device__ __forceinline__ void rank_order(const float (&x)[NK], int n, int rdep
         const bool exact = e < rdepth || (hfit > 0 && (e == 0 || e == hfit - 2 || e == hfit - 1));
         tie |= has_next && exact && ((key[j] ^ other) >> IB) == 0u;
     }
-    if (ballot(tie) != 0ull) {
+    if (ballot(tie) != 0ull && !(COARSE && coarse_row<NK>(x))) {
         uint64_t k64[NK];
 #pragma unroll
         for (int j = 0; j < NK; ++j) {

@@ -155,7 +155,24 @@ first_kernel(CodeTable codes, const uint8_t* __restrict__ block_code, const int6
         uint32_t k1[1] = {in < known ? L.key[slot * 16u + in] : 0xffffffffu};
         sort32<1, 16>(k1);
         const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)k1[0], 0x101, 0xF, 0xF, false);   // row_shl:1
-        const uint64_t ties = ballot(in + 1u < known && ((k1[0] ^ next) >> IB) == 0u);
+        uint64_t ties = ballot(in + 1u < known && ((k1[0] ^ next) >> IB) == 0u);
+        if (ties != 0ull) {
+            // rows on a coarse grid are ranked by their keys all the same (read again:
+            // ties are rare, or all rows are coarse).  3 x 10^5 blocks of LLRs rounded
+            // to whole numbers, us, before the passes / left to the search / so: n = 32
+            // 140 / 133 / 45, n = 127 240 / 256 / 101.
+#pragma unroll 1
+            for (uint32_t j = 0; j < cnt; ++j) {
+                if (((ties >> (16u * j)) & 0xffffull) == 0ull) continue;
+                const uint32_t* w = L.word + ((head + j) & (SLOTS - 1)) * Q::W;
+                const uint32_t n = MIXED ? uniform_u32(w[Q::LEN]) : n0;
+                int64_t row = MIXED ? uniform_i64((int64_t)(((uint64_t)w[Q::ROW + 1] << 32) | w[Q::ROW]))
+                                    : (int64_t)uniform_u32(w[Q::ID]) * n0;
+                float xt[NK];
+                load_row_buf<NK>(make_buf(llr + (row >= 0 ? row : 0), row >= 0 ? n * 4u : 0u), xt, lo);
+                if (coarse_row<NK>(xt)) ties &= ~(0xffffull << (16u * j));
+            }
+        }
         const uint32_t idx = k1[0] & ((1u << IB) - 1u);
         const uint32_t cb = MIXED ? (sub < cnt ? L.code[mt >> 8].w : 0u) : 0u;
         const S col = s_cols[in < known ? cb + idx : 0u];

@@ -410,7 +410,7 @@ __device__ __forceinline__ void match_block(const float (&x)[NK], const uint64_t
         for (;;) {
             if (reach == 0) {                             // the whole block's ranks
                 uint32_t all[NK];
-                rank_order<NK>(x, n, c.rdepth, 0, all);
+                rank_order<NK, NK == 1>(x, n, c.rdepth, 0, all);
 #pragma unroll
                 for (int j = 0; j < NK; ++j) {
                     const int e = lane * NK + j;

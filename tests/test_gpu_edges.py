@@ -1,6 +1,7 @@
 """GPU parity with the CPU oracle, bit for bit, at edges of the match searches and
 of the passes in front of them: results at the first position of a batch order,
-codes of few check bits, ranks past those that the m-line search's sets hold."""
+codes of few check bits, rows whose magnitudes tie, ranks past those that the
+m-line search's sets hold."""
 import os
 
 import numpy as np
@@ -89,6 +90,63 @@ def test_few_check_bits_cost_no_more_than_many(gpu_device):
 
     one, eight = time_of(1), time_of(8)
     assert one <= 1.6 * eight, f"m = 1: {one / 40 * 1e3:.1f} us, m = 8: {eight / 40 * 1e3:.1f} us"
+
+
+def _grid_rows(kind, N, n, rng):
+    """Magnitudes that tie: whole numbers, four levels, one level (coarse grids, whose
+    32-bit keys rank them), thirds (ties that need the full keys), a mixture."""
+    x = (rng.standard_normal((N, n)) * 2.5 - 2.5).astype(np.float32)
+    if kind == "whole":
+        x = np.round(x)
+    elif kind == "levels":
+        x = np.clip(np.round(x / 1.5), -2, 1) + 0.5
+    elif kind == "hard":
+        x = np.sign(x)
+    elif kind == "thirds":
+        x = np.round(x) * np.float32(1 / 3)
+    elif kind == "mixture":
+        x[::2] = np.round(x[::2])
+        x[1::4, ::9] = np.round(x[1::4, ::9])
+        low = np.uint32(3)                               # equal but for the last bits
+        x[3::4, 1::2] = (x[3::4, ::2][:, :n // 2].view(np.uint32) ^ low).view(np.float32)
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("n,m,blocks", [(32, 6, 140000), (60, 40, 30000), (127, 14, DIRECT + 700), (200, 16, DIRECT + 9), (300, 18, 25000)])
+@pytest.mark.parametrize("kind", ["whole", "levels", "hard", "thirds", "mixture"])
+def test_first_pass_of_rows_on_a_grid(gpu_device, n, m, blocks, kind):
+    """Ties among the first pass's candidates: decided by the keys on a coarse grid,
+    left to the search otherwise."""
+    print(f"grid {kind} n={n}", flush=True)
+    H = codes.rlc_H(n, n - m, seed=n)
+    llr = _grid_rows(kind, blocks, n, np.random.default_rng(n))
+    got = binding.orbg_decode(H, torch.from_numpy(llr).to(gpu_device), 300)
+    _check(got, O.decode(H, llr, 300, THREADS), f"grid {kind} n={n}")
+
+
+def test_whole_numbers_cost_little_more(gpu_device):
+    """3 x 10^5 blocks of n = 32: 45 us for rows of whole numbers, 42 for others (133
+    where every tie went to the search)."""
+    print("grid, time", flush=True)
+    H = codes.rlc_H(32, 26, seed=32)
+    g = torch.Generator(device=gpu_device).manual_seed(3)
+    x = torch.empty((300000, 32), device=gpu_device).normal_(-10.0, 6.3, generator=g)
+
+    def time_of(rows):
+        out = binding.orbg_decode(H, rows, 10 ** 4)
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                binding.orbg_decode(H, rows, 10 ** 4, out=out)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    whole, fine = time_of(torch.round(x)), time_of(x)
+    assert whole <= 2 * fine, f"whole numbers {whole / 10:.3f} ms, others {fine / 10:.3f} ms"
 
 
 def _mline(dev, H, llr, budget, segments, tag, jdiv=False):
