@@ -3,15 +3,14 @@
 Default workload: narrow-sense BCH(127,113), t = 2, BPSK over AWGN at
 Eb/N0 = 4.0, 4.5, ..., 7.0 dB, 10^6 blocks per point, query budget 10^5, plain
 ORBGRAND.  One step decodes all 7 x 10^6 blocks (LLRs already resident in HBM)
-with one decode call (light pass + heavy pass).  Prints one JSON line.
+with one decode call (first pass + match search).  Prints one JSON line.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W]
                   [--workload bch127|bch127_1line|rlc32|mixed|learned|stream]
 
 --workload mixed: random linear codes (64,52), (128,116), (256,240) mixed 1:2:1
-in one persistent launch per Eb/N0 point (3..6 dB, 4x10^6 blocks, budget
-10^6), against the same blocks decoded by one launch per code without the
-heavy pass.
+in one decode call per Eb/N0 point (3..6 dB, 4x10^6 blocks, budget 10^6),
+against the same blocks decoded by one call per code, and by the naive launch.
 --workload learned: the learned batch-order proposal on RLC(128,105), trained
 on the GPU, against plain ORBGRAND on the same held-out blocks.
 --workload bch127_1line: the default workload decoded by 1-line ORBGRAND (the
@@ -35,6 +34,9 @@ sys.path.insert(0, ROOT)
 
 import numpy as np  # noqa: E402
 
+# What the decodes by match search print for launch_params: the tuned shapes are passed
+# to them, checked and not used.
+MATCH_SHAPE = "the match search's own"
 METRIC = "decoded blocks/sec and queries/sec at fixed Eb/N0 and equal BLER, 1 MI355X"
 
 # Peak figures (MI355X): 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz one 32-bit integer
@@ -161,14 +163,15 @@ def query_breakdown(q, ab, err, budget, sweep=(10 ** 2, 10 ** 3, 10 ** 4, 10 ** 
     return out
 
 
-# Sources the basic and 1-line decode kernels (light and heavy pass, schedules,
-# launch) are compiled from, and those of the m-line kernel: committed HBM
-# counters stay valid while these are unchanged.
+# Sources the basic and 1-line decode kernels (first pass, match search, light and
+# heavy pass, schedules, launch) are compiled from, and those of the m-line kernels:
+# committed HBM counters stay valid while these are unchanged.
 DECODE_SOURCES = ("decode.hip", "decode_impl.h", "decode_nk1.hip", "decode_nk2.hip", "decode_nk4.hip", "decode_nk8.hip",
                   "decode_nk16.hip", "match_impl.h", "first_impl.h", "match_nk1.hip", "match_nk2.hip", "match_nk4.hip",
                   "match_nk8.hip", "match_nk16.hip", "orbg_device.h", "orbg_internal.h", "orbg_kernels.h", "schedule.hip")
 MLINE_SOURCES = ("mline.hip", "mline_impl.h", "mline_m1.hip", "mline_m2.hip", "mline_m3.hip", "mline_m4.hip", "orbg_mline.h",
                  "mline_match_impl.h", "mline_match_nk1.hip", "mline_match_nk2.hip", "mline_match_nk4.hip", "mline_match_nk8.hip",
+                 "mline_all_nk1.hip", "mline_all_nk2.hip", "mline_all_nk4.hip",
                  "match_impl.h", "decode_impl.h",
                  "orbg_device.h", "orbg_internal.h")
 
@@ -371,7 +374,7 @@ def run_single(args, wl, dev):
         "queries_per_s": q_sum / (wall / args.steps),
         "mean_queries": q_sum / blocks,
         "kernel_ms": float(np.mean(kern_ms)),
-        "launch_params": knobs if knobs else "library defaults",
+        "launch_params": MATCH_SHAPE,
         "per_point": per_point,
         "roofline": {"bound": "alu", "achieved": ops / kavg / 1e12, "peak": PEAK_INT32_OPS / 1e12,
                      "unit": "Tops/s (int32)", "frac": ops / kavg / PEAK_INT32_OPS,
@@ -512,17 +515,17 @@ def run_oneline(args, wl, dev):
 
 
 def run_mixed(args, wl, dev):
-    """Per Eb/N0 point: the tuned persistent mixed launch against two baselines on
-    the same resident buffer, one launch per code over that code's blocks (a
-    one-code mixed call with the code's block list, reading the rows in place):
-    (a) the naive launch -- one one-wave workgroup per block, no work counter, no
-    heavy pass; (b) the persistent light pass without the heavy pass.  Results
-    are compared bit for bit."""
+    """Per Eb/N0 point: one mixed decode call against two baselines on the same
+    resident buffer, one call per code over that code's blocks (a one-code mixed
+    call with the code's block list, reading the rows in place): (a) the naive
+    launch by steps of the query order -- one one-wave workgroup per block, no work
+    counter, no heavy pass; (b) the first pass and match search of one code.
+    Results are compared bit for bit."""
     import torch
     from paper_2202_13951_amd import binding
     params, knobs = tuned_params(args.workload, not args.no_tuned)
     shapes = {"one_block_per_workgroup": binding.LaunchParams(one_block_per_workgroup=1),
-              "persistent_per_code": binding.LaunchParams(split_steps=0)}
+              "one_call_per_code": None}
     stream = torch.cuda.current_stream()
     points, tot_blocks, tot_ms, tot_q = {}, 0, 0.0, 0
     tot_base = {k: 0.0 for k in shapes}
@@ -604,7 +607,7 @@ def run_mixed(args, wl, dev):
         "queries_per_s": tot_q / ksec,
         "baselines_value": {k: tot_blocks / (v / 1e3) for k, v in tot_base.items()},
         "speedup": {k: v / tot_ms for k, v in tot_base.items()},
-        "launch_params": knobs if knobs else "library defaults",
+        "launch_params": MATCH_SHAPE,
         "roofline": {"bound": "alu", "achieved": ops_tot / ksec / 1e12, "peak": PEAK_INT32_OPS / 1e12,
                      "unit": "Tops/s (int32)", "frac": ops_tot / ksec / PEAK_INT32_OPS,
                      "traffic": profiled_traffic(args.workload) if not args.ebn0 else None,
@@ -790,7 +793,7 @@ def run_stream(args, wl, dev):
         "config": {"workload": wl["desc"], "codes": wl["codes"], "rates_per_s": wl["rates"],
                    "ebn0_db_range": list(wl["ebn0_range"]), "budget": wl["budget"],
                    "capacity": wl["capacity"], "max_batch": wl["max_batch"]},
-        "launch_params": knobs if knobs else "library defaults", "per_rate": per_rate,
+        "launch_params": MATCH_SHAPE, "per_rate": per_rate,
     }
 
 
@@ -835,9 +838,8 @@ def run_learned(args, wl, dev):
         ms = time_calls(lambda: out.append(fn()), stream, reps=3)
         return out[-1], ms / 1e3
 
-    shapes = {"defaults": None, "no_heavy_pass": binding.LaunchParams(split_steps=0)}
+    tot = dict(plain_s=0.0, learned_s=0.0)
     points = {}
-    tot = {k: dict(plain_s=0.0, learned_s=0.0) for k in shapes}
     tot_q = dict(blocks=0, plain=0.0, learned=0.0, prior=0.0)
     flops_fwd = 2.0 * (128 * 256 + 256 * 256 + 256 * 64)
     fwd_t, fwd_rows = 0.0, 0
@@ -846,16 +848,11 @@ def run_learned(args, wl, dev):
         N = wl["blocks"]
         binding.orbg_decode(H, llr[:1024], wl["budget"])                    # warm caches
         learned.decode_learned_gated(prop, H, llr[:1024], wl["budget"])
-        pt = {}
-        for name, P in shapes.items():
-            (pc, pq, pab), pt[name] = timed(lambda: binding.orbg_decode_ex(H, llr, wl["budget"], params=P))
-        lt = {}
-        for name, P in shapes.items():
-            (lc, lq, lab, rest), lt[name] = timed(lambda: learned.decode_learned_gated(prop, H, llr, wl["budget"],
-                                                                                      params=P))
+        (pc, pq, pab), t_plain = timed(lambda: binding.orbg_decode(H, llr, wl["budget"]))
+        (lc, lq, lab, rest), t_gated = timed(lambda: learned.decode_learned_gated(prop, H, llr, wl["budget"]))
         po = prior.unsqueeze(0).expand(N, 64).contiguous()
         rc_, rq, rab = binding.orbg_decode_ordered(H, llr, wl["budget"], po)
-        # stages of the gated decode, each timed on its own (default shape)
+        # stages of the gated decode, each timed on its own
         _, t_first = timed(lambda: binding.orbg_decode(H, llr, 64))
         idx = torch.nonzero(pq > 64).flatten()
         sub = llr[idx].contiguous()
@@ -886,36 +883,33 @@ def run_learned(args, wl, dev):
             "queries_diff_vs_plain": mu, "queries_diff_vs_plain_ci95": list(ci),
             "queries_diff_vs_prior": mur, "queries_diff_vs_prior_ci95": list(cir),
             "blocks_network_ran_on": int(rest),
-            "blocks_per_s_plain": {k: N / v for k, v in pt.items()},
-            "blocks_per_s_learned": {k: N / v for k, v in lt.items()},
-            "stage_ms": {"plain_decode": pt["defaults"] * 1e3, "first_batch_pass": t_first * 1e3,
+            "blocks_per_s_plain": N / t_plain,
+            "blocks_per_s_learned": N / t_gated,
+            "stage_ms": {"plain_decode": t_plain * 1e3, "first_batch_pass": t_first * 1e3,
                          "network_fused": t_net * 1e3, "network_forward_only": t_fwd * 1e3,
-                         "ordered_search_of_listed": t_rest * 1e3, "gated_total": lt["defaults"] * 1e3},
+                         "ordered_search_of_listed": t_rest * 1e3, "gated_total": t_gated * 1e3},
             "abandoned_plain": int(pab.sum()), "abandoned_learned": int(lab.sum())}
         print(f"learned {e} dB: {points[f'{e:.1f}']}", file=sys.stderr, flush=True)
         tot_q["blocks"] += N
         tot_q["plain"] += float(pqn.sum())
         tot_q["learned"] += float(lqn.sum())
         tot_q["prior"] += float(rqn.sum())
-        for k in shapes:
-            tot[k]["plain_s"] += pt[k]
-            tot[k]["learned_s"] += lt[k]
+        tot["plain_s"] += t_plain
+        tot["learned_s"] += t_gated
         del llr, sent, pc, pq, pab, lc, lq, lab, rc_, rq, rab, sub, xf, lg, ordr
         torch.cuda.empty_cache()
     Nt = tot_q["blocks"]
     mfma = (flops_fwd * fwd_rows / fwd_t) if fwd_t > 0 else 0.0
     return {
-        "metric": METRIC, "value": Nt / tot["defaults"]["learned_s"], "unit": "blocks/s", "n_gpus": 1,
-        "steps": 1, "warmup": 1, "ms_per_step": tot["defaults"]["learned_s"] * 1e3, "higher_is_better": True,
+        "metric": METRIC, "value": Nt / tot["learned_s"], "unit": "blocks/s", "n_gpus": 1,
+        "steps": 1, "warmup": 1, "ms_per_step": tot["learned_s"] * 1e3, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "u32 syndromes / FP32 LLR (decode), bf16 MFMA with fp32 "
                                                       "accumulation (network)", "data": "synthetic",
         "config": {"workload": wl["desc"], "code": wl["code"], "ebn0_db": wl["ebn0"],
                    "blocks_per_point": wl["blocks"], "budget": wl["budget"], "train_pairs": wl["train_pairs"],
                    "train_ebn0_db": list(wl["train_ebn0"]), "epochs": wl["epochs"], "minibatch": wl["batch"],
                    "lr": wl["lr"], "form": "gated: network only for blocks the first 64 queries do not decide"},
-        "plain_value": Nt / tot["defaults"]["plain_s"],
-        "by_launch_shape": {k: {"plain_blocks_per_s": Nt / v["plain_s"], "learned_blocks_per_s": Nt / v["learned_s"]}
-                            for k, v in tot.items()},
+        "plain_value": Nt / tot["plain_s"],
         "mean_queries_plain": tot_q["plain"] / Nt, "mean_queries_learned": tot_q["learned"] / Nt,
         "mean_queries_prior_order": tot_q["prior"] / Nt,
         "roofline": {"bound": "mfma", "achieved": mfma / 1e12, "peak": 2500.0, "unit": "TFLOP/s (bf16)",

@@ -55,14 +55,15 @@ extern "C" {
  * Launch shape of a decode (the knobs the autotuner sets).  Any field left 0
  * takes the library default (split_steps: -1 takes the default, 0 disables the
  * heavy pass).  They shape the search by steps of 64 queries, which decodes the
- * 1-line order, batch orders of codes with fewer than 9 check bits and codes of
- * n <= 8: a light pass of persistent one-wave workgroups over all blocks, which
- * gives up on a block after `split_steps` steps, and a heavy pass in which
- * workgroups of `heavy_waves` waves each share one such block, taking its steps
- * in turn.  The other decodes (a search over sets of ranks, which has no long
- * blocks to split) take their own launch shape; every field is checked all the
- * same, and one_block_per_workgroup selects the naive launch for them too.  The
- * decoded result does not depend on these values.
+ * 1-line order, batch orders of codes with fewer than 9 check bits, codes of
+ * n <= 8 (one in a mixed decode sends all its codes this way) and any decode for
+ * whose search tables there was no memory: a light pass of persistent one-wave
+ * workgroups over all blocks, which gives up on a block after `split_steps`
+ * steps, and a heavy pass in which workgroups of `heavy_waves` waves each share
+ * one such block, taking its steps in turn.  The other decodes (a search over
+ * sets of ranks, which has no long blocks to split) take their own launch shape;
+ * every field is checked all the same, and one_block_per_workgroup selects the
+ * naive launch for them too.  The decoded result does not depend on these values.
  */
 typedef struct orbg_launch_params {
     int workgroups_per_cu;        /* light pass, 1..64 (default 32) */
@@ -182,7 +183,9 @@ int orbg_decode_1line(const uint8_t* H, const float* llr, int n, int k, uint64_t
  * query has more than 22 flips, which bounds the device tables).  segments_out:
  * DEVICE i32 per block, the number of lines the fit used, or NULL.  The first
  * call on a device builds a 193 MB table of subset counts (allocates and
- * synchronises `stream`).  Errors: ORBG_EINVAL for arguments outside these limits, as
+ * synchronises `stream`), the first for a length lists of rank sets (at most
+ * 14 MB; without them, or under capture, the walk of the order decodes every
+ * block, with the same results).  Errors: ORBG_EINVAL for arguments outside these limits, as
  * orbg_decode otherwise.
  */
 int orbg_decode_mline(const uint8_t* H, const float* llr, int n, int k, uint64_t budget,

@@ -824,9 +824,9 @@ int orbg_decode_learned(const uint8_t* H, const float* llr, int n, int k, uint64
     if (order_out && (e = orbg::mlp_order_table(lw.orders, lw.list, (int64_t)count, batch, order_out, st)) != hipSuccess)
         return fail(ORBG_EHIP, "order table launch failed: %s", hipGetErrorString(e));
     if (count == 0) return ORBG_OK;
-    // 3. ordered decode of the listed blocks from step 1 (blocks still open after
-    // the split point, at least the 64 reordered batches, go to the heavy pass,
-    // which indexes the caller's arrays directly)
+    // 3. ordered decode of the listed blocks, which index the caller's arrays: the
+    // match search, or (few check bits) the steps from step 1, with the heavy pass for
+    // those still open after the split point, at least the 64 reordered batches
     orbg::DecodeArgs b = a;
     b.p = resolve_params(params, true);
     b.list_only = false;

@@ -1,7 +1,8 @@
 // ORBGRAND decode by steps of the query order for gfx950: the 1-line order, batch
-// orders of codes with few check bits, codes of n <= 8, the naive launch and
-// decodes of the first batch alone (list_only).  The other decodes are in
-// match_impl.h and first_impl.h, which share this file's steps 1, 2, 3 and 5.
+// orders of codes with few check bits, codes of n <= 8 (and the codes of a mixed
+// launch that holds one), the naive launch, decodes of the first batch alone
+// (list_only) and any decode whose match tables found no memory.  The other decodes
+// are in match_impl.h and first_impl.h, which share this file's steps 1, 2, 3 and 5.
 //
 // Per block (Algorithm 1 with the basic ORBGRAND generator):
 //   1. stage: the block's LLR row is read coalesced (lane l holds elements

@@ -13,7 +13,7 @@
 // With c ranks known, the patterns of logistic weight <= c are tested.
 //
 // Bound: vector and scalar issue (each wave instruction holds a SIMD for four
-// cycles) beside the one read of every row: 47 vector and 45 scalar instructions
+// cycles) beside the one read of every row: 49 vector and 44 scalar instructions
 // a block.  7 x 10^6 blocks of BCH(127,113), 4 to 7 dB: 1.21 ms, 3.9 TB/s (a
 // large copy reaches 4.75); with the match search of the 14 % it leaves 1.97 ms,
 // where one pass that ranked and walked block by block took 2.80.

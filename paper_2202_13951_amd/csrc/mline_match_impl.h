@@ -21,9 +21,9 @@
 // most blocks takes one or two steps.  10^6 blocks of BCH(127,113) at 5 dB, two
 // lines: 18.0 -> 1.54 ms (the walk of mline_kernel before); 10^5 blocks of n =
 // 256, three lines, 5.5 dB: 38.7 -> 1.07 ms.  Not covered, and left marked in the
-// abandon flag for mline_kernel: results of weight 511 and more, sets of more
-// than seven ranks above 8, sets of two and more with a rank above 254, or past
-// the lists.
+// abandon flag for mline_kernel: results of weight 511 and more (its wide variant
+// takes them up to 2^18 - 2), sets of more than seven ranks above 8, sets of two and
+// more with a rank above 254, or past the lists.
 #pragma once
 #include "match_impl.h"
 #include "orbg_mline.h"

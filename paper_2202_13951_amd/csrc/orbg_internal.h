@@ -30,7 +30,7 @@ struct ClassInfo {
     uint64_t count;
 };
 
-// Tables of the match search (decode_impl.h, match_search): the sets of ranks
+// Tables of the match search (match_impl.h, match_scan): the sets of ranks
 // above 8 a pattern of the schedule can flip, and the counts that give a
 // pattern's position in the order.
 #define ORBG_MATCH_RANKS 128 // ranks whose columns a match search can hold

@@ -156,3 +156,42 @@ def test_inference_kernels_match_the_reference(gpu_device, N):
     for got in (lg, p.logits(learned.features(x))):
         err = np.abs(got.cpu().numpy() - ref).max(axis=1) / np.abs(ref).max(axis=1)
         assert (err <= 1e-2).all(), float(err.max())
+
+
+@pytest.mark.parametrize("which", ["two passes", "few check bits", "small m-line"])
+def test_graph_replay_of_the_search_kernels(gpu_device, which):
+    """Captured decodes whose kernels the other replay tests do not hold: the first pass
+    and the match search behind it, the kernel for few check bits, the one-launch
+    m-line decode.  Every replay, with eager work in between, equals the eager result."""
+    print(f"graph replay {which}", flush=True)
+    n, m, blocks = {"two passes": (100, 14, DIRECT + 3000), "few check bits": (90, 2, 900), "small m-line": (150, 16, 500)}[which]
+    H = codes.rlc_H(n, n - m, seed=n)
+    llr, _ = channel.awgn_llr(codes.generator_matrix(H), blocks, 4.0, seed=n)
+    x = torch.from_numpy(llr).to(gpu_device)
+    out = (torch.zeros((blocks, n), dtype=torch.uint8, device=gpu_device),
+           torch.zeros(blocks, dtype=torch.int64, device=gpu_device), torch.zeros(blocks, dtype=torch.uint8, device=gpu_device))
+
+    def call(rows, dst, stream=None):
+        if which == "small m-line":
+            binding.orbg_decode_mline(H, rows, 3000, 3, segments_out=False, out=dst, stream=stream)
+        else:
+            binding.orbg_decode(H, rows, 3000, out=dst, stream=stream)
+
+    call(x, out)
+    eager = [t.clone() for t in out]
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        call(x, out, s)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        call(x, out, s)
+    other = [torch.empty_like(t) for t in out]
+    for rep in range(3):
+        for t, v in zip(out, (7, -1, 9)):
+            t.fill_(v)
+        call(x.flip(0).contiguous(), other)
+        g.replay()
+        torch.cuda.synchronize()
+        for t, want, swapped in zip(out, eager, other):
+            assert torch.equal(t, want) and torch.equal(swapped.flip(0), want), rep
