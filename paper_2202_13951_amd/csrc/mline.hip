@@ -161,16 +161,18 @@ hipError_t launch_walk(const MlineArgs& a, int grid, hipStream_t stream)
 }  // namespace
 
 // Small batches (up to ORBG_ML_SMALL blocks, n <= 256) go through the searches and the
-// walk in one launch: 64 blocks of n = 127, two lines, 21.2 us, 23.6 as two launches;
-// 500 blocks of n = 256, three lines, 28.0 / 28.9; but 2000 blocks of n = 64, one line,
-// 26.0 / 22.4 and 16 blocks of n = 512, two lines, 63.7 / 54.5 (its registers are cut
-// harder).  Else the narrow search decodes nearly every block and mline_kernel those
-// that it marks: in spans of one flag up to ORBG_ML_SPANS blocks, so that no wave is
-// left with many of them, longer ones above (more waves that only read their flags
-// cost more than they save).  64 blocks of n = 512 that no search covers, two lines,
-// 20000 queries: 11.9 ms, 496 in one span of 64.
+// walk in one launch.  us, one launch / two: n = 127, two lines, 63 blocks 18.8 / 20.9,
+// 1000 blocks 58.9 / 58.0; n = 256, three lines, 300 blocks 88.2 / 88.4, 1000 blocks
+// 143.6 / 143.6; 1000 blocks of n = 64 at 9 dB 15.8 / 18.6.  But 2000 blocks of n = 64
+// 26.0 / 22.4, and 16 blocks of n = 512, two lines, 63.7 / 54.5.
+// Else the narrow search decodes nearly every block and mline_kernel those that it
+// marks, in spans as short as give no more waves than its registers let the chip hold:
+// a wave that only reads its flags costs its launch (8000 blocks of n = 256 at 9 dB,
+// us: spans of one flag 29.5, of three 28.4), and one with many of the marked blocks
+// keeps the others waiting (64 blocks of n = 512 that no search covers, two lines,
+// 20000 queries: one span of 64 496 ms, of one 11.9; 8000 such blocks of n = 256, one
+// line, 30000 queries: of three 5.7 ms, of eight 12.7).
 #define ORBG_ML_SMALL 1024
-#define ORBG_ML_SPANS 8192
 hipError_t launch_mline(const MlineArgs& a, int grid, hipStream_t stream)
 {
     if (a.nblocks <= 0) return hipSuccess;
@@ -182,8 +184,9 @@ hipError_t launch_mline(const MlineArgs& a, int grid, hipStream_t stream)
         if (a.n <= 2 * ORBG_WAVE) return launch_mline_all_nk<2>(w, (int)a.nblocks, stream);
         return launch_mline_all_nk<4>(w, (int)a.nblocks, stream);
     }
-    w.span = 1;
-    while (w.span < ORBG_WAVE && a.nblocks > (int64_t)ORBG_ML_SPANS * w.span) w.span *= 2;
+    const int64_t most = a.n <= 4 * ORBG_WAVE ? 3 * 1024 : 2 * 1024;
+    const int64_t span = (a.nblocks + most - 1) / most;
+    w.span = span < ORBG_WAVE ? (int)span : ORBG_WAVE;
     const int64_t spans = (a.nblocks + w.span - 1) / w.span;
     hipError_t e;
     if (a.n <= ORBG_WAVE) e = launch_mline_match_nk<1>(w, grid, stream);

@@ -1036,24 +1036,28 @@ __device__ __forceinline__ void decode_walk(const Model& md, const uint32_t* tbl
 
 // One wave per block.  The blocks that the narrow search left marked (a.span) go
 // through the wide search and, where that does not cover them either, the walk of the
-// order; ALL: a small batch in one launch, each block through the narrow search too
-// (64 blocks: 21 us, 24 as two launches).  Without the lists (a.span = 0, not ALL)
-// every block is walked.
-// The walk is latency-bound, so the searches inlined before it must not take its
-// waves: the registers are cut for as many as it has alone (its LDS allows four for
-// one or two keys per lane).  MM: the largest number of segments the launch's fits
+// order; ALL: a small batch in one launch, each block through the narrow search too,
+// with syndromes of type T.  Without the lists (a.span = 0, not ALL) every block is
+// walked.
+// The walk is latency-bound, so it wants waves: the registers are cut for as many as
+// they give without scratch memory, the row being read again for the walk and not kept
+// over the wide search.  (5000 blocks of n = 256 that no search covers, one line: 3.8 ms
+// with three waves a SIMD; four for one or two keys per lane take 20 to 80 bytes of
+// scratch a lane, and no time less.)  A small batch has no more than one wave a SIMD, so
+// there they are not cut (63 blocks of n = 127, two lines: 20.5 us cut for four waves
+// with 64-bit syndromes, 18.8 so).  MM: the largest number of segments the launch's fits
 // may use (a.mseg); only the walks up to MM are compiled into the kernel, which keeps
 // the registers of a two-line decode free of the three- and four-line walks' state.
-template <int NK, int MM, bool ALL>
-__global__ void __launch_bounds__(ORBG_WAVE, NK <= 2 ? 4 : 3) mline_kernel(MlineArgs a)
+template <int NK, int MM, bool ALL, typename T>
+__global__ void __launch_bounds__(ORBG_WAVE, ALL ? 1 : NK <= 2 || (NK == 4 && MM <= 2) ? 3 : 2) mline_kernel(MlineArgs a)
 {
     BlockCursor cur(a.span > 0 ? a.abandoned : nullptr, a.nblocks, a.span);
     int64_t b = cur.next();
     if (b < 0) return;
     __shared__ union {
         MlLds<NK * ORBG_WAVE> walk;
-        MmLds<ALL ? NK : 1, uint64_t, false> narrow;
-        MmLds<NK, uint64_t, true> wide;
+        MmLds<ALL ? NK : 1, T, false> narrow;
+        MmLds<NK, T, true> wide;
     } lds;
     auto& S = lds.walk;
     const int lane = lane_id();
@@ -1065,20 +1069,27 @@ __global__ void __launch_bounds__(ORBG_WAVE, NK <= 2 ? 4 : 3) mline_kernel(Mline
     for (; b >= 0; b = cur.next()) {
         const float* row = a.llr + b * (int64_t)n;
         float x[NK];
+        if (ALL || a.span > 0) {
+#pragma unroll
+            for (int j = 0; j < NK; ++j) {
+                const int i = j * ORBG_WAVE + lane;
+                x[j] = i < n ? row[i] : 0.0f;
+            }
+            if constexpr (ALL) {
+                if (mline_match_block<NK, T, false>(a, a.sets, lds.narrow, x, hrow, b) != 0) continue;
+            }
+            if (mline_match_block<NK, T, true>(a, a.sets, lds.wide, x, hrow, b) != 0) continue;
+        }
         bool ybit[NK];
         uint32_t acc = 0;
 #pragma unroll
         for (int j = 0; j < NK; ++j) {
             const int i = j * ORBG_WAVE + lane;
             x[j] = i < n ? row[i] : 0.0f;
-            ybit[j] = i < n && x[j] > 0.0f;
+            ybit[j] = x[j] > 0.0f;
             const uint64_t y = ballot(ybit[j]);
             acc += __popcll(hrow[j] & y);
         }
-        if constexpr (ALL) {
-            if (mline_match_block<NK, uint64_t, false>(a, a.sets, lds.narrow, x, hrow, b) != 0) continue;
-        }
-        if ((ALL || a.span > 0) && mline_match_block<NK, uint64_t, true>(a, a.sets, lds.wide, x, hrow, b) != 0) continue;
         const uint64_t s0 = uniform_u64(ballot((acc & 1u) != 0u));
         bool found = false;
         uint32_t q = a.budget;
@@ -1161,17 +1172,18 @@ __global__ void __launch_bounds__(ORBG_WAVE, NK <= 2 ? 4 : 3) mline_kernel(Mline
 template <int MM>
 hipError_t launch_mline_m(const MlineArgs& a, int grid, hipStream_t stream)
 {
-    if (a.n <= ORBG_WAVE) mline_kernel<1, MM, false><<<grid, ORBG_WAVE, 0, stream>>>(a);
-    else if (a.n <= 2 * ORBG_WAVE) mline_kernel<2, MM, false><<<grid, ORBG_WAVE, 0, stream>>>(a);
-    else if (a.n <= 4 * ORBG_WAVE) mline_kernel<4, MM, false><<<grid, ORBG_WAVE, 0, stream>>>(a);
-    else mline_kernel<8, MM, false><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    if (a.n <= ORBG_WAVE) mline_kernel<1, MM, false, uint64_t><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    else if (a.n <= 2 * ORBG_WAVE) mline_kernel<2, MM, false, uint64_t><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    else if (a.n <= 4 * ORBG_WAVE) mline_kernel<4, MM, false, uint64_t><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    else mline_kernel<8, MM, false, uint64_t><<<grid, ORBG_WAVE, 0, stream>>>(a);
     return hipGetLastError();
 }
 
 template <int NK>
 hipError_t launch_mline_all_nk(const MlineArgs& a, int grid, hipStream_t stream)
 {
-    mline_kernel<NK, ORBG_ML_MSEG, true><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    if (a.m <= 32) mline_kernel<NK, ORBG_ML_MSEG, true, uint32_t><<<grid, ORBG_WAVE, 0, stream>>>(a);
+    else mline_kernel<NK, ORBG_ML_MSEG, true, uint64_t><<<grid, ORBG_WAVE, 0, stream>>>(a);
     return hipGetLastError();
 }
 

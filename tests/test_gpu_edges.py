@@ -248,3 +248,28 @@ def test_mline_blocks_that_no_search_covers_run_side_by_side(gpu_device, n, m, s
         t = best_of(rows, reps)
         limit = 3 * max(alone) + rows.shape[0] / 1024 * sum(alone) / N
         assert t <= limit, f"{rows.shape[0]} blocks {t:.2f} ms; alone {max(alone):.2f} at most, {sum(alone):.2f} in all"
+
+
+@pytest.mark.parametrize("n,m,segments,blocks", [
+    (64, 14, 2, 1024), (64, 14, 2, 1025), (64, 14, 2, 3073), (200, 34, 1, 6145), (64, 14, 3, 64 * 3072 + 1),
+    (512, 20, 2, 2048), (512, 20, 2, 2049), (512, 20, 2, 64 * 2048 + 1)])
+def test_mline_batches_at_the_span_sizes(gpu_device, n, m, segments, blocks):
+    """Batches at the sizes where the marks are read in longer spans: every block gets
+    the answer that it has alone, whichever search takes it."""
+    print(f"mline spans n={n} blocks={blocks}", flush=True)
+    budget, base = 600, 37
+    rng = np.random.default_rng(n + blocks)
+    H = codes.rlc_H(n, n - m, seed=n)
+    cw = channel.encode(codes.generator_matrix(H), rng.integers(0, 2, size=(base, n - m), dtype=np.uint8))
+    rows = 2.0 * cw - 1 + 0.45 * rng.standard_normal((base, n))
+    flat = np.arange(0, base, 5)                     # left to the wide search or to the walk
+    rank = np.argsort(np.argsort(np.abs(rows[flat]), axis=1), axis=1)
+    rows[flat] = np.sign(rows[flat]) * (10 + 0.01 * rank + 0.002 * rng.standard_normal(rank.shape))
+    rows = rows.astype(np.float32)
+    want = O.decode_mline(H, rows, budget, segments, threads=THREADS)[:3]
+    x = torch.from_numpy(rows).to(gpu_device)
+    y = x.repeat((blocks + base - 1) // base, 1)[:blocks].contiguous()
+    got = binding.orbg_decode_mline(H, y, budget, segments)[:3]
+    at = torch.arange(blocks, device=gpu_device) % base
+    for g, w in zip(got, want):
+        assert torch.equal(g.to(torch.int64), torch.from_numpy(w.astype(np.int64)).to(gpu_device)[at])
